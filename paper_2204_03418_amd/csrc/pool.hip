@@ -366,224 +366,257 @@ __global__ __launch_bounds__(kBlock) void pool_steps_kernel(
 
 // Global spatial pooling (the window covers the whole frame: kH = H, kW = W,
 // no spatial padding or dilation, one output per plane and frame), as in a
-// network head.  Lanes hold frames instead of window positions: one wave per
-// (stream, channel) plane stages a block of kPgFrames of its frames -- they
-// lie contiguously in the clip -- into LDS with 16-byte loads (the next
-// block's loads in flight while a block is reduced), and lane t reduces
-// frame t of the block alone, in the order of the per-step kernel's shuffle
-// tree over 64 window lanes (element r in leaf r, the rest neutral), so both
-// paths give the same bits.  The window's frames then come from the lanes
-// below (from the previous block, or the FIFO, across the block's start) and
-// combine in that kernel's temporal tree.  The per-step kernel spends a
-// shuffle tree, a temporal tree and a division on each frame for one value;
-// here each costs one lane.
-constexpr int kPgFrames = 32;  // frames per block, lanes 0..31
+// network head, over a buffer of frames or a whole clip.  Lanes hold frames
+// instead of window positions: a wave stages a block of kPgFrames of a
+// plane's frames -- they lie contiguously in the clip -- into LDS with
+// 16-byte loads (the next block's, or next plane's, in flight while a block is
+// reduced), and lane t reduces frame t of the block alone, in the order of the
+// per-step kernel's shuffle tree over 64 window lanes (element r in leaf r,
+// the rest neutral), so both paths give the same bits.  The reduced frames
+// stay in LDS, the window's span before them first (from the FIFO, then from
+// the block before); lane t's window is kT of them, dT apart, combined in the
+// per-step kernel's temporal tree (KTB leaves; leaves past kT are neutral, so
+// any KTB >= kT gives the same bits).
+//
+// The call is bound by reading the clip.  A workgroup owns kPgWaves * ppw
+// consecutive planes: the FIFO is (slot, plane), so a workgroup reads and
+// writes it in runs of up to 16 planes (64 bytes) instead of one float per
+// slot.  16 streams x 432 channels, 7x7, 64 frames: a 64-frame average in
+// float32 takes 24 us a call (92 MB read and written, 3.8 TB/s; stepping
+// through 64 launches took 399 us), and as the second half of a bfloat16
+// depthwise + pool clip the whole clip takes 55 us (732 us when each output
+// reduced its own 4 x 49 window).
+constexpr int kPgFrames = 64;  // frames per block, one per lane
+constexpr int kPgWaves = 4;
+constexpr int kPgMaxSpan = 128;  // window span f the LDS history is sized for
 
 struct PoolGlobalArgs {
-  int32_t nblk;       // blocks of the call: ceil(count / kPgFrames)
-  int32_t lds_bytes;  // per wave: a block, its alignment and 64 elements of over-read
+  int32_t T, count;   // real frames, all frames (the rest end padding)
+  int32_t nblk;       // blocks of a plane: ceil(count / kPgFrames)
+  int32_t ppw;        // planes per wave
+  int32_t planes;     // B * C
+  int32_t stage;      // LDS bytes of a wave's staged block
   int32_t F;          // window span f = (kT - 1) dT + 1: FIFO slots
-  int64_t tau0;       // output index of the call's first emission
+  int32_t hist0;      // first history entry that exists (max(0, F - 1 - n0))
+  int32_t slot0;      // n0 mod F
+  int32_t t_e0;       // first emitting frame of the call (count: none)
+  int32_t update;     // write the FIFO (0: also in clip mode, which has none)
+  int32_t x_bytes, y_bytes, fstride;
+  FastDiv fd_F, fd_sT;
 };
 
-// Value of `cur` in lane (lane - k) of this block, or of `prev` in the
-// previous block's lane kPgFrames + lane - k.
-__device__ __forceinline__ float lane_back(float cur, float prev, int lane, int k) {
-  const float a = __int_as_float(__builtin_amdgcn_ds_bpermute(((lane - k) & 63) << 2,
-                                                              __float_as_int(cur)));
-  const float b = __int_as_float(__builtin_amdgcn_ds_bpermute(
-      ((kPgFrames + lane - k) & 63) << 2, __float_as_int(prev)));
-  return lane >= k ? a : b;
-}
-
-template <typename T, int KT, bool IS_MAX>
-__global__ __launch_bounds__(64) void pool_steps_global_kernel(
-    PoolGeom g, PoolSteps ps, PoolGlobalArgs pa, const T* __restrict__ x, int64_t x_bc,
-    T* __restrict__ y, int64_t y_bc, float* __restrict__ fifo, int64_t fifo_slot,
-    const float* __restrict__ valid) {
+template <typename T, int KTB, bool IS_MAX>
+__global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
+    PoolGeom g, PoolGlobalArgs pa, const T* __restrict__ x, int64_t x_bc, T* __restrict__ y,
+    int64_t y_bc, float* __restrict__ fifo, int64_t fifo_slot, float* __restrict__ valid) {
   extern __shared__ uint4 pg_lds[];
   constexpr uint32_t esz = sizeof(T);
-  constexpr int NU = esz == 2 ? 5 : 9;  // 16-byte units per lane and block
+  constexpr int NU = esz == 2 ? 9 : 17;  // 16-byte units per lane and block
   constexpr bool is_max = IS_MAX;
   const float neutral = is_max ? -INFINITY : 0.f;
-  const int lane = int(threadIdx.x);
-  const int bc = int(blockIdx.x);  // one wave per plane
-  const int S = g.H * g.W;
-  const int plane = int(uint32_t(bc) * uint32_t(x_bc) * esz);
-  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x, ps.x_bytes);
-  const __amdgpu_buffer_rsrc_t yr = make_rsrc(y, ps.y_bytes);
-  const int yplane = int(uint32_t(bc) * uint32_t(y_bc) * esz);
+  const int tid = int(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = g.H * g.W, F = pa.F, kT = g.kT, dT = g.dT;
+  const int per = kPgWaves * pa.ppw;          // planes of this workgroup
+  const int bc0 = int(blockIdx.x) * per;
+  // only an average over the real frames reads the validity flags
+  const bool counted = !is_max && !g.count_include_pad;
+  char* lds = reinterpret_cast<char*>(pg_lds);
+  char* stage = lds + wave * pa.stage;
+  const int hlen = F - 1 + kPgFrames;
+  float* hist = reinterpret_cast<float*>(lds + kPgWaves * pa.stage);
+  float* okay = hist + per * hlen;  // the history's flags, alike for all planes
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x, pa.x_bytes);
+  const __amdgpu_buffer_rsrc_t yr = make_rsrc(y, pa.y_bytes);
 
-  // the previous block's reduced frames and validity by lane; before the
-  // first block, lanes kPgFrames - (F - 1) + q hold the FIFO's frame
-  // n0 - (F - 1) + q (the window spans F = (kT - 1) dT + 1 frames)
-  const int F = pa.F;
-  float prev = neutral, prevok = 0.f;
-  {
-    const int q = lane - (kPgFrames - (F - 1));
-    const int64_t rf = ps.n0 - (F - 1) + q;
-    if (q >= 0 && lane < kPgFrames && rf >= 0) {
-      prev = fifo[(rf % F) * fifo_slot + bc];
-      prevok = valid[rf % F];
-    }
+  // history entry i of a plane is frame n0 - (F - 1) + i, in slot
+  // (n0 + 1 + i) mod F; entries before the stream began are start padding
+  for (int e = tid; e < (F - 1) * per; e += 64 * kPgWaves) {
+    const int i = e / per, q = e - i * per;
+    const int v = pa.slot0 + 1 + i;
+    const int slot = v - fdiv(v, pa.fd_F) * F;
+    const bool have = i >= pa.hist0 && bc0 + q < pa.planes;
+    hist[q * hlen + i] = have ? fifo[int64_t(slot) * fifo_slot + bc0 + q] : neutral;
   }
+  if (counted)
+    for (int i = tid; i < F - 1; i += 64 * kPgWaves) {
+      const int v = pa.slot0 + 1 + i;
+      okay[i] = i >= pa.hist0 ? valid[v - fdiv(v, pa.fd_F) * F] : 0.f;
+    }
+  __syncthreads();
 
-  // block b's real frames from the 16-byte boundary at or below their first
-  // byte; units past them read the out-of-range offset, and the one unit
-  // that runs past the clip's end is read element by element
+  // block b of local plane q: its real frames in 16-byte units from the
+  // 16-byte boundary at or below their first byte; units past them read the
+  // out-of-range offset.  A last unit that would run past the clip's end is
+  // left to `tail` single elements, read when the block is staged (once a call)
   struct Block {
-    int s0, a0, units;
+    int s0, a0, units, tail;
   };
-  auto block = [&](int b) {
+  auto block = [&](int q, int b) {
     Block k;
     const int t0 = b * kPgFrames;
-    const int nr = min(max(ps.T - t0, 0), kPgFrames);
-    k.s0 = plane + t0 * ps.fstride;
+    const int nr = min(max(pa.T - t0, 0), kPgFrames);
+    k.s0 = int(uint32_t(bc0 + q) * uint32_t(x_bc) * esz) + t0 * pa.fstride;
     k.a0 = k.s0 & ~15;
-    k.units = nr > 0 ? (k.s0 + nr * ps.fstride - k.a0 + 15) >> 4 : 0;
+    const int bytes = nr > 0 ? k.s0 + nr * pa.fstride - k.a0 : 0;
+    const bool whole = k.a0 + ((bytes + 15) & ~15) <= pa.x_bytes;
+    k.units = whole ? (bytes + 15) >> 4 : bytes >> 4;
+    k.tail = whole ? 0 : (bytes & 15) / int(esz);
     return k;
   };
   auto fetch = [&](const Block& k, uint4 (&v)[NU]) {
 #pragma unroll
     for (int j = 0; j < NU; ++j) {
       const int u = j * 64 + lane;
-      const int off = k.a0 + u * 16;
-      const bool whole = u < k.units && off + 16 <= ps.x_bytes;
-      const auto v4 = __builtin_amdgcn_raw_buffer_load_b128(xr, whole ? off : kOutOfRange, 0, 0);
+      const auto v4 = __builtin_amdgcn_raw_buffer_load_b128(
+          xr, u < k.units ? k.a0 + u * 16 : kOutOfRange, 0, 0);
       v[j] = make_uint4(v4[0], v4[1], v4[2], v4[3]);
-      if (u < k.units && off + 16 > ps.x_bytes) {
-        uint32_t h[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if constexpr (esz == 2) {
-            const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(
-                xr, off + 4 * e + 2 <= ps.x_bytes ? off + 4 * e : kOutOfRange, 0, 0);
-            const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(
-                xr, off + 4 * e + 4 <= ps.x_bytes ? off + 4 * e + 2 : kOutOfRange, 0, 0);
-            h[e] = lo | (hi << 16);
-          } else {
-            h[e] = __builtin_amdgcn_raw_buffer_load_b32(
-                xr, off + 4 * e + 4 <= ps.x_bytes ? off + 4 * e : kOutOfRange, 0, 0);
-          }
-        }
-        v[j] = make_uint4(h[0], h[1], h[2], h[3]);
-      }
     }
   };
+  // a wave's LDS operations complete in order: only the compiler has to keep
+  // the staged block's writes, its reads and the next block's writes apart
+  auto order = [] {
+    __builtin_amdgcn_wave_barrier();
+    __asm__ volatile("" ::: "memory");
+  };
+  auto comb = [&](float a, float c) { return is_max ? fmaxf(a, c) : a + c; };
 
+  const int q0 = wave * pa.ppw;
+  const int nq = min(pa.ppw, pa.planes - bc0 - q0);  // this wave's planes (<= 0: none)
   uint4 v[NU];
-  Block cb = block(0);
+  Block cb = block(q0, 0);
+  if (nq <= 0) cb.units = cb.tail = 0;
   fetch(cb, v);
-  for (int b = 0; b < pa.nblk; ++b) {
+  for (int q = q0; q < q0 + nq; ++q) {
+    float* hq = hist + q * hlen;
+    const int yplane = int(uint32_t(bc0 + q) * uint32_t(y_bc) * esz);
+    for (int b = 0; b < pa.nblk; ++b) {
 #pragma unroll
-    for (int j = 0; j < NU; ++j)
-      if (j * 64 + lane < cb.units) pg_lds[j * 64 + lane] = v[j];
-    __syncthreads();  // (one wave: its LDS writes land before the reads)
-    const int shift = cb.s0 - cb.a0;
-    if (b + 1 < pa.nblk) {
-      cb = block(b + 1);
-      fetch(cb, v);
-    }
-
-    // lane t: frame t0 + t, its S elements in leaves 0..S-1.  The leaf
-    // masks are built from a vector copy of S made here, in the loop: as
-    // loop invariants the compiler would hoist all 64 of them, as scalar
-    // lane masks, out of the loop and spill them
-    int Sv;
-    __asm__ volatile("v_mov_b32 %0, %1" : "=v"(Sv) : "s"(S));
-    const uint32_t nb = __float_as_uint(neutral);
-    const int t = b * kPgFrames + lane;
-    const bool live = lane < kPgFrames;
-    const char* fb =
-        reinterpret_cast<const char*>(pg_lds) + shift + (live ? lane : 0) * ps.fstride;
-    auto leaf = [&](int r) {
-      float xv;
-      if constexpr (esz == 2)
-        xv = __uint_as_float(uint32_t(*reinterpret_cast<const uint16_t*>(fb + 2 * r)) << 16);
-      else
-        xv = *reinterpret_cast<const float*>(fb + 4 * r);
-      // as the per-step kernel: the neutral value, combined with the element
-      const float lv = is_max ? fmaxf(neutral, xv) : neutral + xv;
-      const uint32_t keep = uint32_t((r - Sv) >> 31);  // all ones when r < S
-      return __uint_as_float((__float_as_uint(lv) & keep) | (nb & ~keep));
-    };
-    auto comb = [&](float a, float c) { return is_max ? fmaxf(a, c) : a + c; };
-    float tr[32];
-#pragma unroll
-    for (int l = 0; l < 32; ++l) tr[l] = comb(leaf(l), leaf(l + 32));
-#pragma unroll
-    for (int m = 16; m > 0; m >>= 1)
-#pragma unroll
-      for (int l = 0; l < m; ++l) tr[l] = comb(tr[l], tr[l + m]);
-    const bool real = live && t < ps.T;
-    const float cur = real ? tr[0] : neutral;
-    const float curok = real ? 1.f : 0.f;
-    __syncthreads();  // the reads are done before the next block's writes
-
-    // the window of step n = n0 + t: frames n - (KT - 1 - q) dT, q = 0..KT-1
-    // (the temporal stride only decides which steps emit)
-    const int64_t n = ps.n0 + t;
-    float fv[KT], fok[KT];
-    fv[KT - 1] = cur;
-    fok[KT - 1] = curok;
-#pragma unroll
-    for (int q = 0; q + 1 < KT; ++q) {
-      fv[q] = lane_back(cur, prev, lane, (KT - 1 - q) * g.dT);
-      fok[q] = lane_back(curok, prevok, lane, (KT - 1 - q) * g.dT);
-    }
-    float tv[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const bool in = q < KT && n - int64_t(KT - 1 - q) * g.dT >= 0;
-      tv[q] = in ? fv[q < KT ? q : 0] : neutral;
-    }
-#pragma unroll
-    for (int m = 4; m > 0; m >>= 1) {
-      float nv[8];
-#pragma unroll
-      for (int l = 0; l < 8; ++l) nv[l] = is_max ? fmaxf(tv[l], tv[l ^ m]) : tv[l] + tv[l ^ m];
-#pragma unroll
-      for (int l = 0; l < 8; ++l) tv[l] = nv[l];
-    }
-    float out = tv[0];
-    if (!is_max) {
-      float div = float(KT * S);
-      if (!g.count_include_pad) {
-        float tc[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const bool in = q < KT && n - int64_t(KT - 1 - q) * g.dT >= 0;
-          tc[q] = in ? fok[q < KT ? q : 0] : 0.f;
-        }
-#pragma unroll
-        for (int m = 4; m > 0; m >>= 1) {
-          float nc[8];
-#pragma unroll
-          for (int l = 0; l < 8; ++l) nc[l] = tc[l] + tc[l ^ m];
-#pragma unroll
-          for (int l = 0; l < 8; ++l) tc[l] = nc[l];
-        }
-        div = tc[0] * float(S);
+      for (int j = 0; j < NU; ++j)
+        if (j * 64 + lane < cb.units) reinterpret_cast<uint4*>(stage)[j * 64 + lane] = v[j];
+      if (lane < cb.tail) {
+        const int off = cb.units * 16 + lane * int(esz);
+        if constexpr (esz == 2)
+          *reinterpret_cast<uint16_t*>(stage + off) =
+              uint16_t(__builtin_amdgcn_raw_buffer_load_b16(xr, cb.a0 + off, 0, 0));
+        else
+          *reinterpret_cast<uint32_t*>(stage + off) =
+              __builtin_amdgcn_raw_buffer_load_b32(xr, cb.a0 + off, 0, 0);
       }
-      out = div > 0.f ? out / div : 0.f;
+      order();
+      const int shift = cb.s0 - cb.a0;
+      const bool more = b + 1 < pa.nblk;
+      if (more || q + 1 < q0 + nq) {
+        cb = more ? block(q, b + 1) : block(q + 1, 0);
+        fetch(cb, v);
+      }
+
+      // lane t: frame t0 + t, its S elements in leaves 0..S-1.  The leaf
+      // masks are built from a vector copy of S made here, in the loop: as
+      // loop invariants the compiler would hoist all 64 of them, as scalar
+      // lane masks, out of the loop and spill them
+      int Sv;
+      __asm__ volatile("v_mov_b32 %0, %1" : "=v"(Sv) : "s"(S));
+      const uint32_t nb = __float_as_uint(neutral);
+      const int t = b * kPgFrames + lane;
+      const bool real = t < pa.T;
+      const char* fb = stage + shift + (real ? lane : 0) * pa.fstride;
+      auto leaf = [&](int r) {
+        float xv;
+        if constexpr (esz == 2)
+          xv = __uint_as_float(uint32_t(*reinterpret_cast<const uint16_t*>(fb + 2 * r)) << 16);
+        else
+          xv = *reinterpret_cast<const float*>(fb + 4 * r);
+        // as the per-step kernel: the neutral value, combined with the element
+        const float lv = is_max ? fmaxf(neutral, xv) : neutral + xv;
+        const uint32_t keep = uint32_t((r - Sv) >> 31);  // all ones when r < S
+        return __uint_as_float((__float_as_uint(lv) & keep) | (nb & ~keep));
+      };
+      float tr[32];
+      if (S > 32) {  // uniform
+#pragma unroll
+        for (int l = 0; l < 32; ++l) tr[l] = comb(leaf(l), leaf(l + 32));
+      } else {
+#pragma unroll
+        for (int l = 0; l < 32; ++l) tr[l] = leaf(l);
+      }
+#pragma unroll
+      for (int m = 16; m > 0; m >>= 1)
+#pragma unroll
+        for (int l = 0; l < m; ++l) tr[l] = comb(tr[l], tr[l + m]);
+      hq[F - 1 + lane] = real ? tr[0] : neutral;
+      order();
+
+      // the window of frame t: history entries t0 + t + q dT of the block
+      // (from a copy of kT made here, for the reason given at the leaves)
+      int kTs = kT;
+      __asm__ volatile("" : "+s"(kTs));
+      float tv[KTB];
+#pragma unroll
+      for (int a = 0; a < KTB; ++a) {
+        tv[a] = neutral;
+        if (a < kTs) tv[a] = hq[lane + a * dT];  // uniform
+      }
+#pragma unroll
+      for (int m = KTB / 2; m > 0; m >>= 1)
+#pragma unroll
+        for (int l = 0; l < m; ++l) tv[l] = comb(tv[l], tv[l + m]);
+      float out = tv[0];
+      if constexpr (!is_max) {
+        float div = float(kT * S);
+        if (counted) {
+          float cnt = 0.f;  // whole numbers: any order
+          for (int a = 0; a < kT; ++a) {
+            const int e = b * kPgFrames + lane + a * dT - (F - 1);  // frame of the call
+            cnt += e < 0 ? okay[F - 1 + e] : e < pa.T ? 1.f : 0.f;
+          }
+          div = cnt * float(S);
+        }
+        out = div > 0.f ? out / div : 0.f;
+      }
+      const int te = t - pa.t_e0;
+      const int k = te >= 0 ? fdiv(te, pa.fd_sT) : 0;  // the call's k-th output
+      const bool emits = t < pa.count && te >= 0 && te == k * g.sT;
+      store_at(yr, emits ? yplane + k * int(esz) : kOutOfRange, 0, from_f32<T>(out));
+
+      // the span before the next block: the block's last F - 1 frames
+      const int nf = min(kPgFrames, pa.count - b * kPgFrames);
+      for (int i0 = 0; i0 < F - 1; i0 += 64) {
+        const int i = i0 + lane;
+        const float h = hq[min(i, F - 2) + nf];
+        order();
+        if (i < F - 1) hq[i] = h;
+        order();
+      }
     }
-    const bool emits = live && t < ps.count && n >= g.d && (n - g.d) % g.sT == 0;
-    const int64_t k = emits ? (n - g.d) / g.sT - pa.tau0 : 0;  // the call's k-th output
-    store_at(yr, emits ? yplane : kOutOfRange, emits ? int(k * int64_t(esz)) : 0,
-             from_f32<T>(out));
-    // the call's last F - 1 frames go to their FIFO slots
-    if (ps.update && live && t < ps.count && t >= ps.count - (F - 1))
-      fifo[(n % F) * fifo_slot + bc] = cur;
-    prev = cur;
-    prevok = curok;
   }
+  if (!pa.update) return;
+  __syncthreads();
+  // the call's last F - 1 frames go to their FIFO slots: history entry i is
+  // frame n0 + count - (F - 1) + i
+  const int first = max(0, F - 1 - pa.count);
+  for (int e = first * per + tid; e < (F - 1) * per; e += 64 * kPgWaves) {
+    const int i = e / per, q = e - i * per;
+    const int v = pa.slot0 + pa.count + 1 + i;
+    const int slot = v - fdiv(v, pa.fd_F) * F;
+    if (bc0 + q < pa.planes) fifo[int64_t(slot) * fifo_slot + bc0 + q] = hist[q * hlen + i];
+  }
+  // nobody reads the flags of this layer in this launch (otherwise they are
+  // written by a launch of their own)
+  if (!counted && blockIdx.x == 0)
+    for (int t = max(0, pa.count - F) + tid; t < pa.count; t += 64 * kPgWaves) {
+      const int v = pa.slot0 + t;
+      valid[v - fdiv(v, pa.fd_F) * F] = t < pa.T ? 1.f : 0.f;
+    }
 }
 
-// Validity flags of the FIFO slots the call's frames went to (one thread).
+// Validity flags of the FIFO slots the call's frames went to (one wave; the
+// last R frames have a slot each).
 __global__ void pool_valid_kernel(float* valid, int32_t R, int64_t n0, int32_t count, int32_t T) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const int32_t first = count > R ? count - R : 0;
-  for (int32_t t = first; t < count; ++t) valid[(n0 + t) % R] = t < T ? 1.f : 0.f;
+  for (int32_t t = first + int32_t(threadIdx.x); t < count; t += 64)
+    valid[(n0 + t) % R] = t < T ? 1.f : 0.f;
 }
 
 __global__ void pool_header_kernel(StateHeader h, StateHeader* dst) {
@@ -633,33 +666,81 @@ hipError_t launch_pool_init(const PoolGeom& g, const PoolLayout& L, char* state,
   return hipGetLastError();
 }
 
-hipError_t launch_pool_clip(const PoolGeom& g, int32_t T, int32_t T_out, const void* x, void* y,
-                            hipStream_t s) {
-  const int64_t total = int64_t(g.B) * g.C * T_out * g.So();
-  if (total == 0) return hipSuccess;
-  if (g.dtype == CO_BF16)
-    hipLaunchKernelGGL(pool_clip_kernel<bf16_t>, dim3(grid_for(total)), dim3(kBlock), 0, s, g, T,
-                       T_out, static_cast<const bf16_t*>(x), static_cast<bf16_t*>(y));
-  else
-    hipLaunchKernelGGL(pool_clip_kernel<float>, dim3(grid_for(total)), dim3(kBlock), 0, s, g, T,
-                       T_out, static_cast<const float*>(x), static_cast<float*>(y));
+namespace {
+
+// Global spatial pooling over small frames (H * W <= 64: one window element
+// per lane of the per-step kernel's groups) with a window span the kernel's
+// history holds: the frames-in-lanes kernel, any temporal stride and dilation.
+bool pool_global_fits(const PoolGeom& g) {
+  return g.kH == g.H && g.kW == g.W && g.pH == 0 && g.pW == 0 && g.dH == 1 && g.dW == 1 &&
+         g.H * g.W <= 64 && g.kT <= 64 && g.f <= kPgMaxSpan;
+}
+
+// state null: clip mode (a stream that begins and ends with the clip).
+template <typename T, int KTB>
+hipError_t pool_global_launch(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
+                              int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
+                              int64_t n0, bool update, hipStream_t s) {
+  const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
+  PoolGlobalArgs pa;
+  pa.T = nreal;
+  pa.count = count;
+  pa.nblk = int32_t((int64_t(count) + kPgFrames - 1) / kPgFrames);
+  pa.planes = int32_t(int64_t(g.B) * g.C);
+  // planes per wave: runs of 16 planes of the FIFO per workgroup where that
+  // leaves a workgroup per CU, else more workgroups
+  pa.ppw = 4;
+  while (pa.ppw > 1 && pa.planes / (kPgWaves * pa.ppw) < 256) pa.ppw /= 2;
+  pa.F = g.f;
+  pa.hist0 = int32_t(std::max<int64_t>(0, g.f - 1 - n0));
+  pa.slot0 = int32_t(n0 % g.f);
+  const int64_t te = n0 >= g.d ? (g.sT - (n0 - g.d) % g.sT) % g.sT : g.d - n0;
+  pa.t_e0 = int32_t(std::min<int64_t>(te, count));
+  pa.update = update && state ? 1 : 0;
+  pa.x_bytes = int32_t(((int64_t(g.B) * g.C - 1) * x_bc + int64_t(nreal) * g.S()) * esz);
+  pa.y_bytes = int32_t(int64_t(g.B) * g.C * y_bc * esz);
+  pa.fstride = int32_t(g.S() * esz);
+  pa.fd_F = make_fastdiv(uint32_t(g.f));
+  pa.fd_sT = make_fastdiv(uint32_t(g.sT));
+  // a block, its alignment shift and the 64-element over-read of the last lane
+  const int64_t rows = std::min<int64_t>(kPgFrames, nreal);
+  pa.stage = int32_t(((rows * g.S() + 64) * esz + 32 + 15) / 16 * 16);
+  const int per = kPgWaves * pa.ppw;
+  const int lds = kPgWaves * pa.stage + (per * (pa.F - 1 + kPgFrames) + pa.F) * 4;
+  float* fifo = state ? reinterpret_cast<float*>(state + L.fifo) : nullptr;
+  float* valid = state ? reinterpret_cast<float*>(state + L.valid) : nullptr;
+  auto kern = g.kind == CO_POOL_MAX ? pool_steps_global_kernel<T, KTB, true>
+                                     : pool_steps_global_kernel<T, KTB, false>;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3(unsigned((int64_t(pa.planes) + per - 1) / per)),
+                     dim3(64 * kPgWaves), lds, s, g, pa, static_cast<const T*>(x), x_bc,
+                     static_cast<T*>(y), y_bc, fifo, L.fifo_slot_elems, valid);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !pa.update) return e;
+  if (g.kind == CO_POOL_MAX || g.count_include_pad) return e;  // written in the launch
+  hipLaunchKernelGGL(pool_valid_kernel, dim3(1), dim3(64), 0, s, valid, g.R, n0, count, nreal);
   return hipGetLastError();
 }
 
-namespace {
-
-template <typename T, int KT>
-hipError_t pool_global_launch(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
-                              int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
-                              int64_t n0, bool update, hipStream_t s);
-bool pool_global_fits(const PoolGeom& g);
+template <typename T>
+hipError_t pool_global_t(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
+                         int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
+                         int64_t n0, bool update, hipStream_t s) {
+  const auto launch = g.kT <= 8    ? pool_global_launch<T, 8>
+                      : g.kT <= 16 ? pool_global_launch<T, 16>
+                      : g.kT <= 32 ? pool_global_launch<T, 32>
+                                   : pool_global_launch<T, 64>;
+  return launch(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
+}
 
 template <typename T, int G, int KT>
 hipError_t pool_steps_launch(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
                              int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
                              int64_t n0, bool update, hipStream_t s) {
-  if (pool_global_fits(g))
-    return pool_global_launch<T, KT>(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
   PoolSteps ps;
   ps.n0 = n0;
   ps.count = count;
@@ -691,50 +772,6 @@ hipError_t pool_steps_launch(const PoolGeom& g, const PoolLayout& L, char* state
   return hipGetLastError();
 }
 
-// Global spatial pooling over small frames with the per-step kernel's
-// 64-lane window groups (16 < H*W <= 64): the frames-in-lanes kernel.
-bool pool_global_fits(const PoolGeom& g) {
-  const int kHW = g.kH * g.kW;
-  return g.kH == g.H && g.kW == g.W && g.pH == 0 && g.pW == 0 && g.dH == 1 && g.dW == 1 &&
-         g.Ho == 1 && g.Wo == 1 && kHW > 16 && kHW <= 64;
-}
-
-template <typename T, int KT>
-hipError_t pool_global_launch(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
-                              int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
-                              int64_t n0, bool update, hipStream_t s) {
-  PoolSteps ps{};  // (the emission fields go in pa)
-  ps.n0 = n0;
-  ps.count = count;
-  ps.T = nreal;
-  ps.emit0 = n0 > g.d ? n0 : g.d;
-  ps.sT = g.sT;
-  ps.update = update ? 1 : 0;
-  const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
-  ps.x_bytes = int32_t(((int64_t(g.B) * g.C - 1) * x_bc + int64_t(nreal) * g.S()) * esz);
-  ps.y_bytes = int32_t(int64_t(g.B) * g.C * y_bc * esz);
-  ps.fstride = int32_t(g.S() * esz);
-  PoolGlobalArgs pa;
-  pa.nblk = int32_t((int64_t(count) + kPgFrames - 1) / kPgFrames);
-  pa.F = g.R;  // the FIFO holds the window's span
-  const int64_t lo = n0 > g.d ? n0 : g.d;
-  pa.tau0 = (lo - g.d + g.sT - 1) / g.sT;
-  // the block, its alignment shift and the 64-element over-read of the last lane
-  pa.lds_bytes = int32_t(((kPgFrames * g.S() + 64) * esz + 16 + 15) / 16 * 16);
-  if (pa.lds_bytes > 64 * 16 * (esz == 2 ? 5 : 9)) return hipErrorInvalidValue;  // NU units
-  float* fifo = reinterpret_cast<float*>(state + L.fifo);
-  float* valid = reinterpret_cast<float*>(state + L.valid);
-  auto kern = g.kind == CO_POOL_MAX ? pool_steps_global_kernel<T, KT, true>
-                                     : pool_steps_global_kernel<T, KT, false>;
-  hipLaunchKernelGGL(kern, dim3(unsigned(int64_t(g.B) * g.C)), dim3(64), pa.lds_bytes, s, g, ps,
-                     pa, static_cast<const T*>(x), x_bc, static_cast<T*>(y), y_bc, fifo,
-                     L.fifo_slot_elems, valid);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !update) return e;
-  hipLaunchKernelGGL(pool_valid_kernel, dim3(1), dim3(64), 0, s, valid, g.R, n0, count, nreal);
-  return hipGetLastError();
-}
-
 template <typename T, int G>
 hipError_t pool_steps_kt(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
                          int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
@@ -753,6 +790,8 @@ template <typename T>
 hipError_t pool_steps_t(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
                         int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
                         int64_t n0, bool update, hipStream_t s) {
+  if (pool_global_fits(g))
+    return pool_global_t<T>(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
   const int kHW = g.kH * g.kW;
   if (kHW > 16) return pool_steps_kt<T, 64>(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
   if (kHW > 4) return pool_steps_kt<T, 16>(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
@@ -769,12 +808,10 @@ hipError_t launch_pool_valid(float* valid, int32_t R, int64_t n0, int32_t count,
 
 bool pool_steps_supported(const PoolGeom& g, int64_t x_frames, int64_t y_frames) {
   const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
-  // temporal stride or dilation above 1: the frames-in-lanes global pool,
-  // whose window reaches (kT - 1) dT lanes back across one block; the lane
-  // group kernel, whose window is the last kT frames, takes a stride alone
-  const bool strided = g.sT != 1 || g.dT != 1;
-  const bool general = pool_global_fits(g) ? int64_t(g.kT - 1) * g.dT < kPgFrames : g.dT == 1;
-  return (!strided || general) && g.kT >= 1 && g.kT <= 5 && g.kH * g.kW <= 64 &&  // (kT <= 8: tree)
+  // the lane-group kernel's window is the last kT <= 5 frames: any temporal
+  // stride, no dilation
+  const bool group = g.dT == 1 && g.kT >= 1 && g.kT <= 5 && g.kH * g.kW <= 64;
+  return (pool_global_fits(g) || group) &&
          int64_t(g.B) * g.C * x_frames * g.S() * esz < (int64_t(1) << 31) &&
          int64_t(g.B) * g.C * y_frames * g.So() * esz < (int64_t(1) << 31);
 }
@@ -785,6 +822,27 @@ hipError_t launch_pool_steps(const PoolGeom& g, const PoolLayout& L, char* state
   if (g.dtype == CO_BF16)
     return pool_steps_t<bf16_t>(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
   return pool_steps_t<float>(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
+}
+
+hipError_t launch_pool_clip(const PoolGeom& g, int32_t T, int32_t T_out, const void* x, void* y,
+                            hipStream_t s) {
+  const int64_t total = int64_t(g.B) * g.C * T_out * g.So();
+  if (total == 0) return hipSuccess;
+  // a clip is a stream that begins with it and ends with its end padding
+  // (Principles 2 and 4), so the frames-in-lanes kernel serves it without a
+  // state; other windows reduce every output's window on its own
+  if (pool_global_fits(g) && pool_steps_supported(g, T, T_out)) {
+    const auto launch = g.dtype == CO_BF16 ? pool_global_t<bf16_t> : pool_global_t<float>;
+    return launch(g, PoolLayout{}, nullptr, x, int64_t(T) * g.S(), T, T + g.pT, y,
+                  int64_t(T_out), 0, false, s);
+  }
+  if (g.dtype == CO_BF16)
+    hipLaunchKernelGGL(pool_clip_kernel<bf16_t>, dim3(grid_for(total)), dim3(kBlock), 0, s, g, T,
+                       T_out, static_cast<const bf16_t*>(x), static_cast<bf16_t*>(y));
+  else
+    hipLaunchKernelGGL(pool_clip_kernel<float>, dim3(grid_for(total)), dim3(kBlock), 0, s, g, T,
+                       T_out, static_cast<const float*>(x), static_cast<float*>(y));
+  return hipGetLastError();
 }
 
 }  // namespace coinf
