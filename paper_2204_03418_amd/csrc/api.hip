@@ -168,6 +168,20 @@ struct Scratch {
   int64_t bytes;
 };
 
+// How a forward_steps call over T frames of clip x runs: as one launch of a
+// family's persistent kernel or of the clip GEMM, or as a loop of steps.
+enum class StepsRoute { Loop, Depthwise, Direct, Gemm, Reg, Clip };
+
+StepsRoute steps_route(const ConvGeom& g, int32_t T, int32_t y_cap_frames, const void* x) {
+  if (dw_steps_supported(g, T, y_cap_frames)) return StepsRoute::Depthwise;
+  if (direct_steps_supported(g, T, y_cap_frames)) return StepsRoute::Direct;
+  const bool gemm = gemm_steps_supported(g, T, y_cap_frames, x);
+  const bool reg = reg_steps_supported(g, T, y_cap_frames);
+  if (clip_gemm_supported(g, T, y_cap_frames) && clip_gemm_preferred(g, T, gemm, reg))
+    return StepsRoute::Clip;
+  return gemm ? StepsRoute::Gemm : reg ? StepsRoute::Reg : StepsRoute::Loop;
+}
+
 co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* y,
                              int32_t y_cap_frames, int32_t pad_end, int32_t update_state,
                              hipStream_t s, int32_t* n_out, const Scratch* sc) {
@@ -180,19 +194,37 @@ co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* 
   if (n_emit > y_cap_frames) return CO_EINVAL;
   if (n_emit > 0 && !y) return CO_EINVAL;
   const int64_t n0 = h->n;
-  const bool dw = dw_steps_supported(g, T, y_cap_frames);
-  const bool dir = direct_steps_supported(g, T, y_cap_frames);
-  const bool gem = gemm_steps_supported(g, T, y_cap_frames, x);
-  if (count > 0 && (dw || dir || gem || reg_steps_supported(g, T, y_cap_frames))) {
-    // one persistent launch: partial sums stay on chip across frames; with
+  const StepsRoute route = count > 0 ? steps_route(g, T, y_cap_frames, x) : StepsRoute::Loop;
+  if (route != StepsRoute::Loop) {
+    // one launch: partial sums stay on chip across frames; with
     // update_state = 0 the state is simply not written back
-    const auto launch = dw    ? launch_conv_steps_depthwise
-                        : dir ? launch_conv_steps_direct
-                        : gem ? launch_conv_steps_gemm
-                              : launch_conv_steps_reg;
-    const co_status st = hip_status(launch(g, h->L, h->state, x, int64_t(T) * g.S(), T,
-                                           int32_t(count), y, int64_t(y_cap_frames) * g.So(),
-                                           n0, update_state != 0, s));
+    const int64_t x_bc = int64_t(T) * g.S(), y_bc = int64_t(y_cap_frames) * g.So();
+    const bool update = update_state != 0;
+    hipError_t e = hipErrorInvalidValue;
+    switch (route) {
+      case StepsRoute::Depthwise:
+        e = launch_conv_steps_depthwise(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0,
+                                        update, s);
+        break;
+      case StepsRoute::Direct:
+        e = launch_conv_steps_direct(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0,
+                                     update, s);
+        break;
+      case StepsRoute::Gemm:
+        e = launch_conv_steps_gemm(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0,
+                                   update, s);
+        break;
+      case StepsRoute::Reg:
+        e = launch_conv_steps_reg(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0,
+                                  update, s);
+        break;
+      case StepsRoute::Clip:
+        e = launch_conv_clip_gemm(g, h->L, h->state, x, T, int32_t(count), y, y_bc, n0, update,
+                                  CO_ACT_NONE, s);
+        break;
+      case StepsRoute::Loop: break;
+    }
+    const co_status st = hip_status(e);
     if (st != CO_OK) return st;
     if (update_state) h->n += count;
     *n_out = int32_t(n_emit);
@@ -417,12 +449,7 @@ co_status co_conv_steps_fused(const co_conv_handle* h, int32_t T, int32_t y_cap_
   // (the GEMM family also needs 4-byte aligned pixel pairs in x; an
   // allocation from the caching allocator always is)
   static const uint32_t aligned_probe = 0;
-  *fused = dw_steps_supported(g, T, y_cap_frames) ||
-                   direct_steps_supported(g, T, y_cap_frames) ||
-                   gemm_steps_supported(g, T, y_cap_frames, &aligned_probe) ||
-                   reg_steps_supported(g, T, y_cap_frames)
-               ? 1
-               : 0;
+  *fused = steps_route(g, T, y_cap_frames, &aligned_probe) != StepsRoute::Loop ? 1 : 0;
   return CO_OK;
 }
 
@@ -465,8 +492,11 @@ co_status co_conv_forward_ws(const co_conv_desc* desc, const void* weight, const
                                   bn->eps, workspace, workspace_bytes, stream, &h)
           : co_conv_init_state(desc, weight, bias, workspace, workspace_bytes, stream, &h);
   if (st != CO_OK) return st;
+  // (a one-launch call need not leave a state behind; a loop keeps its
+  // partial sums in it)
+  const int32_t update = steps_route(g, T, int32_t(T_out), x) == StepsRoute::Loop ? 1 : 0;
   int32_t n = 0;
-  st = conv_forward_steps(h, x, T, y, int32_t(T_out), 1, 1, as_stream(stream), &n, nullptr);
+  st = conv_forward_steps(h, x, T, y, int32_t(T_out), 1, update, as_stream(stream), &n, nullptr);
   co_conv_destroy(h);
   if (st == CO_OK && n != T_out) return CO_EINVAL;  // (Principle 4: cannot happen)
   return st;

@@ -134,6 +134,18 @@ bool gemm_steps_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames,
 hipError_t launch_conv_steps_gemm(const ConvGeom& g, const ConvLayout& L, char* state,
                                   const void* x, int64_t x_bc, int32_t T, int32_t count, void* y,
                                   int64_t y_bc, int64_t n0, bool update, hipStream_t stream);
+// forward_steps as one implicit GEMM over the buffer's frames (conv_clip.hip):
+// any GEMM-family layer without the two-wave tap split, any kT, stride and
+// dilation; same bits as stepping.  act applies to the emitted, rounded
+// frames as launch_act would.
+bool clip_gemm_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames);
+// Whether it is the faster way for a supported call, against the persistent
+// GEMM or register-GEMM kernel where one of them takes the call, else
+// against single steps.
+bool clip_gemm_preferred(const ConvGeom& g, int64_t x_frames, bool gemm_steps, bool reg_steps);
+hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* state,
+                                 const void* x, int32_t T, int32_t count, void* y, int64_t y_bc,
+                                 int64_t n0, bool update, int32_t act, hipStream_t stream);
 hipError_t launch_pack_gemm_steps(const ConvGeom& g, const ConvLayout& L, char* state,
                                   const void* weight, const float* wscale, hipStream_t stream);
 // Weight packing: wscale (float32, C_out) multiplies each output channel's

@@ -1,0 +1,67 @@
+"""forward_steps as one implicit GEMM over the frames, at the edges of its
+tiles and forms: pixel pairs over odd and even planes (also of one pixel),
+windows that fit LDS and that do not, channel counts that fill no tile or
+fragment, every weight packing, temporal strides and dilations, spatial
+strides, one temporal tap, and the channel tile that only large calls take.
+Each against the oracle and bit for bit against single steps, as a clip, as
+the continuation of single steps, before them, and without updating the state.
+"""
+import pytest
+import torch
+
+from paper_2204_03418_amd import coinf, synth
+from parity_util import oracle_conv, say
+from test_gpu_parity import DEV, _check_fused_steps
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, Cin, Cout, kernel, size, stride, padding, dilation, dtype, T, algo
+    (3, 40, 40, (9, 1), (25,), (1, 1), (4, 0), (1, 1), "bf16", 70, "auto"),   # window, ragged C
+    (2, 64, 128, (5, 1), (18,), (1, 1), (0, 0), (1, 1), "bf16", 33, "auto"),  # window, even plane
+    (2, 256, 64, (9, 1), (17,), (1, 1), (8, 0), (1, 1), "bf16", 30, "auto"),  # window past LDS
+    (2, 96, 96, (4, 1), (25,), (1, 1), (1, 0), (3, 1), "bf16", 40, "auto"),   # dilation, pairs
+    (2, 48, 64, (4, 1), (25,), (2, 1), (3, 0), (2, 1), "bf16", 40, "auto"),   # strided: no pairs
+    (5, 64, 48, (3,), (), (1,), (1,), (1,), "bf16", 130, "auto"),             # one pixel a frame
+    (3, 20, 33, (4, 1), (7,), (1, 1), (2, 0), (1, 1), "f32", 90, "gemm_reg"),  # fp32, ragged
+    (2, 48, 48, (3, 3, 3), (9, 11), (1, 1, 1), (1, 1, 1), (1, 1, 1), "bf16", 40, "auto"),
+    (2, 32, 64, (2, 3, 3), (15, 13), (1, 2, 2), (1, 1, 1), (1, 1, 1), "bf16", 40, "auto"),
+    (2, 40, 72, (2, 3, 3), (7, 9), (2, 1, 1), (0, 1, 1), (1, 1, 1), "bf16", 64, "gemm"),
+    (2, 64, 80, (3, 3, 3), (8, 8), (2, 1, 1), (1, 1, 1), (1, 1, 1), "bf16", 64, "gemm_ws"),
+    (4, 36, 64, (3, 3, 3), (10, 9), (1, 1, 1), (2, 1, 1), (1, 1, 1), "f32", 64, "gemm"),
+    (64, 32, 192, (1, 3, 3), (8, 8), (1, 1, 1), (0, 1, 1), (1, 1, 1), "bf16", 20, "auto"),
+    (3, 72, 54, (1, 1, 1), (5, 5), (1, 1, 1), (0, 0, 0), (1, 1, 1), "bf16", 12, "auto"),
+    (2, 24, 130, (1, 1, 1), (6, 7), (1, 1, 1), (0, 0, 0), (1, 1, 1), "f32", 12, "auto"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(map(str, c[:4])) + c[8])
+def test_clip_gemm_steps(case):
+    B, cin, cout, k, size, st, p, dil, dt, T, algo = case
+    say("clip gemm", case)
+    spec = synth.ConvSpec(batch=B, in_channels=cin, out_channels=cout, kernel=k, in_size=size,
+                          stride=st, padding=p, dilation=dil, dtype=dt)
+    x, w, b = synth.conv_inputs(spec, T, 97000 + 7 * cin + cout, "kaiming")
+
+    def make():
+        return coinf.CoConv(w.to(DEV), b.to(DEV), batch=B, in_size=size, stride=st, padding=p,
+                            dilation=dil, algo=algo)
+
+    _check_fused_steps(make, x, oracle_conv(w, b, st, p, dil, 1), synth.torch_dtype(dt),
+                       "clip gemm")
+
+
+def test_clip_gemm_unaligned_clip():
+    """A clip that starts one element past an aligned address and whose planes
+    hold an odd number of pixels: the pair loads and four-pixel stores take
+    any 2-byte alignment."""
+    say("clip gemm unaligned")
+    spec = synth.ConvSpec(batch=2, in_channels=33, out_channels=48, kernel=(3, 1), in_size=(5,),
+                          dtype="bf16")
+    x, w, b = synth.conv_inputs(spec, 31, 97999, "kaiming")
+    flat = torch.zeros(x.numel() + 1, dtype=x.dtype, device=DEV)
+    flat[1:].copy_(x.reshape(-1).to(DEV))
+    xu = flat[1:].view(x.shape)
+    a, c = (coinf.CoConv(w.to(DEV), b.to(DEV), batch=2, in_size=(5,)) for _ in range(2))
+    assert xu.data_ptr() % 4 == 2 and a.steps_fused(31)
+    assert torch.equal(a.forward_steps(xu), c.forward_steps(x.to(DEV)))
