@@ -553,6 +553,20 @@ co_status co_bneck_forward_steps(co_bneck_handle* h, const void* x, int32_t T, v
                                  int32_t z_cap_frames, int32_t update_state, void* stream,
                                  int32_t* n_out);
 
+/* The same with a device workspace for the pointwise frames, when it holds at
+ * least two of the call's frames: per chunk of as many frames as fit, one
+ * launch of the pointwise convolution over the chunk and one of the depthwise
+ * convolution and the pool, with the bits of the launch per frame.  Falls back
+ * to a launch per frame where those do not take the layers, and with
+ * update_state = 0 unless one chunk holds the call.  workspace may be NULL; it
+ * is free for reuse once the call's work on the stream is done.
+ * co_bneck_workspace_bytes: what the library would like for T frames (0: a
+ * launch per frame anyway).  Host only. */
+co_status co_bneck_workspace_bytes(const co_bneck_handle* h, int32_t T, int64_t* bytes);
+co_status co_bneck_forward_steps_ws(co_bneck_handle* h, const void* x, int32_t T, void* z,
+                                    int32_t z_cap_frames, int32_t update_state, void* workspace,
+                                    int64_t workspace_bytes, void* stream, int32_t* n_out);
+
 co_status co_bneck_destroy(co_bneck_handle* h);
 
 /*

@@ -158,6 +158,9 @@ co_bneck_bind = _sig("co_bneck_bind", i32, [vp, i32, vp, i32, vp, pvp])
 co_bneck_forward_step = _sig("co_bneck_forward_step", i32, [vp, vp, vp, i32, vp])
 co_bneck_forward_steps = _sig("co_bneck_forward_steps", i32,
                               [vp, vp, i32, vp, i32, i32, vp, pi32])
+co_bneck_workspace_bytes = _sig("co_bneck_workspace_bytes", i32, [vp, i32, pi64])
+co_bneck_forward_steps_ws = _sig("co_bneck_forward_steps_ws", i32,
+                                 [vp, vp, i32, vp, i32, i32, vp, i64, vp, pi32])
 co_bneck_destroy = _sig("co_bneck_destroy", i32, [vp])
 co_residual_align = _sig("co_residual_align", i32, [i64, i64, i64, i64, pi64, pi64, pi64])
 
@@ -814,10 +817,13 @@ class Bottleneck:
         cap = pool_out_frames(p.desc, p.steps, conv_out_frames(c.desc, c.steps, T))
         z = torch.empty((p.batch, p.channels, cap) + p.out_size, dtype=p.torch_dtype,
                         device=x.device)
-        n = i32()
-        check(co_bneck_forward_steps(self.handle, _ptr(x), T, _ptr(z), cap,
-                                     1 if update_state else 0, _stream(), ctypes.byref(n)),
-              "co_bneck_forward_steps")
+        n, nb = i32(), i64()
+        check(co_bneck_workspace_bytes(self.handle, T, ctypes.byref(nb)),
+              "co_bneck_workspace_bytes")
+        ws = torch.empty(nb.value, dtype=torch.uint8, device=x.device) if nb.value else None
+        check(co_bneck_forward_steps_ws(self.handle, _ptr(x), T, _ptr(z), cap,
+                                        1 if update_state else 0, _ptr(ws), nb.value, _stream(),
+                                        ctypes.byref(n)), "co_bneck_forward_steps_ws")
         return z if n.value else None
 
     def forward(self, x):

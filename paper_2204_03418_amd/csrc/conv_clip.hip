@@ -79,7 +79,8 @@ struct ClipArgs {
   int32_t shift;     // pixels by which the tiles begin early (see PAIR)
   int32_t m_pairs, n_tiles;  // (pixel tile, stream) pairs; channel tiles
   int32_t y_bytes, w_bytes, ring_bytes;
-  int32_t plane;     // elements between input channels (T * S)
+  int32_t plane;     // elements between input channels
+  int32_t span;      // of them, the call's: T * S
   int32_t y_bc;      // elements between output channels
   int32_t ring_slot;
   int32_t nq, ntaps;  // k-steps per temporal tap; spatial taps
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
 
   // the stream's planes only: channels past C_in read out of range (zero)
   const __amdgpu_buffer_rsrc_t xr =
-      make_rsrc(x + int64_t(b) * g.Cin * ca.plane, g.Cin * ca.plane * esz);
+      make_rsrc(x + int64_t(b) * g.Cin * ca.plane, ((g.Cin - 1) * ca.plane + ca.span) * esz);
   const __amdgpu_buffer_rsrc_t yr = make_rsrc(y, ca.y_bytes);
   const __amdgpu_buffer_rsrc_t rr = make_rsrc(ring, ca.ring_bytes);
   const __amdgpu_buffer_rsrc_t br = make_rsrc(bias, g.Cout * 4);
@@ -239,8 +240,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
             const int qa = q0 + rb * 128 + 2 * lane;
             // where a pair reaches over the end of the planes, load the pair
             // beside it (a plane has two pixels at least)
-            sh[n] = qa < 0 ? 1 : qa == ca.plane - 1 ? -1 : 0;
-            const bool in = (qa >= -1) & (qa < ca.plane) & (i < CSn * nrb);
+            sh[n] = qa < 0 ? 1 : qa == ca.span - 1 ? -1 : 0;
+            const bool in = (qa >= -1) & (qa < ca.span) & (i < CSn * nrb);
             uint32_t vo = in ? uint32_t((qa + sh[n]) + (cb * 32 + wave * 8) * ca.plane) * 2u
                              : uint32_t(kOutOfRange);
 #pragma unroll
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
           // where a pair reaches over the end of the planes, load the pair
           // beside it (a plane has two pixels at least)
           const int qa = base[i] + tap;
-          const int sh = qa < 0 ? 1 : qa == ca.plane - 1 ? -1 : 0;
+          const int sh = qa < 0 ? 1 : qa == ca.span - 1 ? -1 : 0;
           mode[i] = sh;
           moved[i] = __ballot((sh != 0) & (va | vb));
           voff[i] = (va | vb) ? (qa + sh) * esz : kOutOfRange;
@@ -825,8 +826,8 @@ bool clip_gemm_preferred(const ConvGeom& g, int64_t x_frames, bool gemm_steps, b
 }
 
 hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* state,
-                                 const void* x, int32_t nreal, int32_t count, void* y,
-                                 int64_t y_bc, int64_t n0, bool update, int32_t act,
+                                 const void* x, int64_t x_bc, int32_t nreal, int32_t count,
+                                 void* y, int64_t y_bc, int64_t n0, bool update, int32_t act,
                                  hipStream_t s) {
   const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
   ClipCall c{&g, &L, state, x, y, ClipArgs{}, s};
@@ -847,7 +848,8 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   ca.slot0 = int32_t(tau0 % g.R);
   ca.R = g.R;
   ca.tail = update && ca.nu > ca.E ? 1 : 0;
-  ca.plane = int32_t(int64_t(nreal) * g.S());
+  ca.plane = int32_t(x_bc);
+  ca.span = int32_t(int64_t(nreal) * g.S());
   ca.y_bc = int32_t(y_bc);
   ca.y_bytes = int32_t(int64_t(g.B) * g.Cout * y_bc * esz);
   ca.w_bytes = int32_t(L.weight_bytes);
@@ -893,7 +895,7 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   ca.fd_wcols = make_fastdiv(uint32_t(ca.wcols));
   const int tile = clip_tile(g, ca.E);
   if (g.dtype == CO_F32) return clip_dispatch<float, false, false>(c, tile);
-  if (!clip_pairs(g) || ca.plane < 2) return clip_dispatch<bf16_t, false, false>(c, tile);
+  if (!clip_pairs(g) || ca.span < 2) return clip_dispatch<bf16_t, false, false>(c, tile);
   // slots wrap around to output E at the pixel (E mod R) So of a tile row
   ca.shift = ca.tail ? int32_t((int64_t(ca.E % g.R) * ca.So) & 1) : 0;
   // the tile's pixels and those its later taps add, in LDS at once

@@ -491,6 +491,7 @@ struct CpSteps {
   int32_t fstride;  // bytes between consecutive frames of a plane
   int32_t PW;       // padded tile width: W + 2 pW
   int32_t tfirst;   // first frame of the call whose convolution step emits
+  int32_t act;      // activation of the convolution's rounded frames
   int64_t n0p;      // pool steps before the call
   int64_t emit0p;   // first pool step of the call that emits: max(n0p, pool delay)
   FastDiv fd_Cout, fd_Wo, fd_W;
@@ -592,7 +593,8 @@ __global__ __launch_bounds__(64) void convpool_steps_kernel(
 #pragma unroll
       for (int e = 0; e < NS; ++e) a = fmaf(wr[j][e], xv[e], a);
       if (j == KT - 1) {
-        const float yv = to_f32<T>(from_f32<T>(a + bo));
+        float yv = to_f32<T>(from_f32<T>(a + bo));
+        if (cs.act == CO_ACT_RELU) yv = fmaxf(yv, 0.f);  // uniform
         const float lf = is_max ? fmaxf(neutral, yv) : neutral + yv;
         row[lane] = from_f32<T>(pl ? lf : neutral);
       } else {
@@ -719,7 +721,7 @@ __global__ __launch_bounds__(64) void convpool_steps_kernel(
 template <typename T, int KH, int KW, int KT, int PKT>
 hipError_t cps_launch(const ConvGeom& g, const ConvLayout& L, char* cstate, const PoolGeom& pg,
                       const PoolLayout& PL, char* pstate, const void* x, int32_t T_in, void* z,
-                      int64_t z_cap, int64_t n0c, int64_t n0p, bool update, hipStream_t s) {
+                      int64_t z_cap, int64_t n0c, int64_t n0p, bool update, int32_t act, hipStream_t s) {
   CpSteps cs;
   const int64_t v0 = n0c + g.pT;
   cs.v0 = int32_t(v0 < (int64_t(1) << 29) ? v0 : (int64_t(1) << 29));
@@ -733,6 +735,7 @@ hipError_t cps_launch(const ConvGeom& g, const ConvLayout& L, char* cstate, cons
   cs.PW = g.W + 2 * g.pW;
   const int64_t tf = int64_t(g.kT - 1) - v0;
   cs.tfirst = int32_t(tf > 0 ? tf : 0);
+  cs.act = act;
   cs.n0p = n0p;
   cs.emit0p = n0p > pg.d ? n0p : pg.d;
   cs.fd_Cout = make_fastdiv(uint32_t(g.Cout));
@@ -758,12 +761,12 @@ hipError_t cps_launch(const ConvGeom& g, const ConvLayout& L, char* cstate, cons
 template <typename T, int KH, int KW, int KT>
 hipError_t cps_pkt(const ConvGeom& g, const ConvLayout& L, char* cstate, const PoolGeom& pg,
                    const PoolLayout& PL, char* pstate, const void* x, int32_t T_in, void* z,
-                   int64_t z_cap, int64_t n0c, int64_t n0p, bool update, hipStream_t s) {
+                   int64_t z_cap, int64_t n0c, int64_t n0p, bool update, int32_t act, hipStream_t s) {
   switch (pg.kT) {
 #define CO_CPS_CASE(P)                                                                        \
     case P:                                                                                   \
       return cps_launch<T, KH, KW, KT, P>(g, L, cstate, pg, PL, pstate, x, T_in, z, z_cap,    \
-                                          n0c, n0p, update, s);
+                                          n0c, n0p, update, act, s);
     CO_CPS_CASE(1) CO_CPS_CASE(2) CO_CPS_CASE(3) CO_CPS_CASE(4) CO_CPS_CASE(5)
 #undef CO_CPS_CASE
     default: return hipErrorInvalidValue;
@@ -773,12 +776,12 @@ hipError_t cps_pkt(const ConvGeom& g, const ConvLayout& L, char* cstate, const P
 template <typename T, int KH, int KW>
 hipError_t cps_kt(const ConvGeom& g, const ConvLayout& L, char* cstate, const PoolGeom& pg,
                   const PoolLayout& PL, char* pstate, const void* x, int32_t T_in, void* z,
-                  int64_t z_cap, int64_t n0c, int64_t n0p, bool update, hipStream_t s) {
+                  int64_t z_cap, int64_t n0c, int64_t n0p, bool update, int32_t act, hipStream_t s) {
   switch (g.kT) {
 #define CO_CPS_CASE(K)                                                                        \
     case K:                                                                                   \
       return cps_pkt<T, KH, KW, K>(g, L, cstate, pg, PL, pstate, x, T_in, z, z_cap, n0c, n0p, \
-                                   update, s);
+                                   update, act, s);
     CO_CPS_CASE(1) CO_CPS_CASE(2) CO_CPS_CASE(3) CO_CPS_CASE(4) CO_CPS_CASE(5)
 #undef CO_CPS_CASE
     default: return hipErrorInvalidValue;
@@ -788,11 +791,11 @@ hipError_t cps_kt(const ConvGeom& g, const ConvLayout& L, char* cstate, const Po
 template <typename T>
 hipError_t cps_dispatch(const ConvGeom& g, const ConvLayout& L, char* cstate, const PoolGeom& pg,
                         const PoolLayout& PL, char* pstate, const void* x, int32_t T_in, void* z,
-                        int64_t z_cap, int64_t n0c, int64_t n0p, bool update, hipStream_t s) {
+                        int64_t z_cap, int64_t n0c, int64_t n0p, bool update, int32_t act, hipStream_t s) {
   if (g.kH == 3 && g.kW == 3)
-    return cps_kt<T, 3, 3>(g, L, cstate, pg, PL, pstate, x, T_in, z, z_cap, n0c, n0p, update, s);
+    return cps_kt<T, 3, 3>(g, L, cstate, pg, PL, pstate, x, T_in, z, z_cap, n0c, n0p, update, act, s);
   if (g.kH == 1 && g.kW == 1)
-    return cps_kt<T, 1, 1>(g, L, cstate, pg, PL, pstate, x, T_in, z, z_cap, n0c, n0p, update, s);
+    return cps_kt<T, 1, 1>(g, L, cstate, pg, PL, pstate, x, T_in, z, z_cap, n0c, n0p, update, act, s);
   return hipErrorInvalidValue;
 }
 
@@ -916,12 +919,13 @@ bool convpool_steps_supported(const ConvGeom& g, const PoolGeom& pg, int64_t T) 
 hipError_t launch_convpool_steps(const ConvGeom& g, const ConvLayout& L, char* cstate,
                                  const PoolGeom& pg, const PoolLayout& PL, char* pstate,
                                  const void* x, int32_t T, void* z, int64_t z_cap, int64_t n0c,
-                                 int64_t n0p, bool update, hipStream_t s) {
+                                 int64_t n0p, bool update, int32_t act,
+                                 hipStream_t s) {
   if (!convpool_steps_supported(g, pg, T) || T <= 0) return hipErrorInvalidValue;
   if (g.dtype == CO_BF16)
-    return cps_dispatch<bf16_t>(g, L, cstate, pg, PL, pstate, x, T, z, z_cap, n0c, n0p, update,
+    return cps_dispatch<bf16_t>(g, L, cstate, pg, PL, pstate, x, T, z, z_cap, n0c, n0p, update, act,
                                 s);
-  return cps_dispatch<float>(g, L, cstate, pg, PL, pstate, x, T, z, z_cap, n0c, n0p, update, s);
+  return cps_dispatch<float>(g, L, cstate, pg, PL, pstate, x, T, z, z_cap, n0c, n0p, update, act, s);
 }
 
 hipError_t launch_convpool_step(const ConvGeom& g, const ConvLayout& L, char* cstate,

@@ -144,8 +144,9 @@ bool clip_gemm_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames);
 // against single steps.
 bool clip_gemm_preferred(const ConvGeom& g, int64_t x_frames, bool gemm_steps, bool reg_steps);
 hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* state,
-                                 const void* x, int32_t T, int32_t count, void* y, int64_t y_bc,
-                                 int64_t n0, bool update, int32_t act, hipStream_t stream);
+                                 const void* x, int64_t x_bc, int32_t T, int32_t count, void* y,
+                                 int64_t y_bc, int64_t n0, bool update, int32_t act,
+                                 hipStream_t stream);
 hipError_t launch_pack_gemm_steps(const ConvGeom& g, const ConvLayout& L, char* state,
                                   const void* weight, const float* wscale, hipStream_t stream);
 // Weight packing: wscale (float32, C_out) multiplies each output channel's
@@ -177,11 +178,12 @@ hipError_t launch_convpool_step(const ConvGeom& g, const ConvLayout& L, char* cs
 // handles' step counters n0c (convolution) and n0p (pool): the pooled
 // outputs go to z (B, C, z_cap, 1, 1) from frame 0; with update the ring, the
 // FIFO and the FIFO's validity flags advance (the host advances the counters).
+// act applies to the convolution's rounded frames, as launch_act would.
 bool convpool_steps_supported(const ConvGeom& g, const PoolGeom& pg, int64_t T);
 hipError_t launch_convpool_steps(const ConvGeom& g, const ConvLayout& L, char* cstate,
                                  const PoolGeom& pg, const PoolLayout& PL, char* pstate,
                                  const void* x, int32_t T, void* z, int64_t z_cap, int64_t n0c,
-                                 int64_t n0p, bool update, hipStream_t stream);
+                                 int64_t n0p, bool update, int32_t act, hipStream_t stream);
 
 // Fused X3D-style bottleneck step (convpool.hip): a pointwise (1x1x1,
 // direct-packed, delay 0) convolution with activation act1, a depthwise

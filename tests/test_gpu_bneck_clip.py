@@ -1,0 +1,59 @@
+"""The fused bottleneck's forward_steps with a workspace: the pointwise frames
+of a chunk as one GEMM, then the depthwise convolution and the pool over them.
+Whole-call, uneven and two-frame chunks, and workspaces too small to use,
+against the launch per frame bit for bit, with and without updating the state.
+"""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2204_03418_amd import coinf, synth
+from parity_util import say
+from test_gpu_bneck import BNECK_CASES, DEV, _bneck_parts
+
+pytestmark = pytest.mark.gpu
+
+
+def _steps(bn, x, cap, frames, update):
+    p, w = bn.pool, bn.pw
+    z = torch.full((p.batch, p.channels, cap) + p.out_size, float("nan"), dtype=p.torch_dtype,
+                   device=DEV)
+    frame = w.batch * w.out_channels * w.in_size[0] * w.in_size[1] * x.element_size()
+    ws = torch.empty(max(frames * frame, 1), dtype=torch.uint8, device=DEV)
+    n = coinf.i32()
+    st = coinf.co_bneck_forward_steps_ws(
+        bn.handle, ctypes.c_void_p(x.data_ptr()), x.shape[2], ctypes.c_void_p(z.data_ptr()), cap,
+        1 if update else 0, ctypes.c_void_p(ws.data_ptr()), frames * frame,
+        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), ctypes.byref(n))
+    assert st == coinf.CO_OK
+    return z[:, :, :n.value]
+
+
+@pytest.mark.parametrize("frames", [0, 1, 2, 5, 16])
+@pytest.mark.parametrize("case", BNECK_CASES, ids=lambda c: f"bneck_{c[6]}_{c[-1]}_{c[1]}")
+def test_bottleneck_chunks(case, frames):
+    say("bneck chunks", case, frames)
+    B, ci, size, dt, T = case[0], case[1], case[3], case[-1], 16
+    xd = synth.normal((B, ci, T) + size, 5600 + ci, dtype=dt).to(DEV)
+    _, modules, _, _ = _bneck_parts(case, 5610 + ci)
+
+    def make():
+        pw, dw, pool = modules()
+        return coinf.Bottleneck(pw, case[8], dw, case[9], pool)
+
+    ref, got = make(), make()
+    want = [z for z in (ref.forward_step(xd[:, :, t].contiguous()) for t in range(T))
+            if z is not None]
+    st = [m.state.clone() for m in (got.pw, got.dw, got.pool)]
+    peek = _steps(got, xd, T, frames, False)
+    torch.cuda.synchronize()
+    assert all(torch.equal(m.state, s) for m, s in zip((got.pw, got.dw, got.pool), st))
+    assert (got.pw.steps, got.dw.steps, got.pool.steps) == (0, 0, 0)
+    head = _steps(got, xd[:, :, :T - 3].contiguous(), T, frames, True)
+    tail = [got.forward_step(xd[:, :, t].contiguous()) for t in range(T - 3, T)]
+    outs = [head[:, :, i] for i in range(head.shape[2])] + [z for z in tail if z is not None]
+    assert (got.pw.steps, got.dw.steps) == (T, T) and got.pool.steps == ref.pool.steps
+    assert len(outs) == len(want) == peek.shape[2]
+    for i, w in enumerate(want):
+        assert torch.equal(outs[i], w) and torch.equal(peek[:, :, i], w)
