@@ -170,10 +170,14 @@ struct Scratch {
 
 // How a forward_steps call over T frames of clip x runs: as one launch of a
 // family's persistent kernel or of the clip GEMM, or as a loop of steps.
-enum class StepsRoute { Loop, Depthwise, Direct, Gemm, Reg, Clip };
+enum class StepsRoute { Loop, Depthwise, DirectMma, Direct, Gemm, Reg, Clip };
 
 StepsRoute steps_route(const ConvGeom& g, int32_t T, int32_t y_cap_frames, const void* x) {
   if (dw_steps_supported(g, T, y_cap_frames)) return StepsRoute::Depthwise;
+  if (direct_mma_layer(g))
+    return direct_mma_fits(g, int64_t(T) * g.S(), T, int64_t(y_cap_frames) * g.So())
+               ? StepsRoute::DirectMma
+               : StepsRoute::Loop;
   if (direct_steps_supported(g, T, y_cap_frames)) return StepsRoute::Direct;
   const bool gemm = gemm_steps_supported(g, T, y_cap_frames, x);
   const bool reg = reg_steps_supported(g, T, y_cap_frames);
@@ -205,6 +209,10 @@ co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* 
       case StepsRoute::Depthwise:
         e = launch_conv_steps_depthwise(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0,
                                         update, s);
+        break;
+      case StepsRoute::DirectMma:
+        e = launch_direct_mma(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0, update,
+                              s);
         break;
       case StepsRoute::Direct:
         e = launch_conv_steps_direct(g, h->L, h->state, x, x_bc, T, int32_t(count), y, y_bc, n0,
@@ -350,9 +358,11 @@ co_status co_conv_init_state(const co_conv_desc* desc, const void* weight, const
   co_status st = conv_geom(desc, &g);
   if (st != CO_OK) return st;
   if (g.has_bias && !bias) return CO_EINVAL;
-  const ConvLayout L = conv_layout(g);
+  ConvLayout L = conv_layout(g);
   if (state_bytes < L.total) return CO_ESTATE;
-  StateHeader hdr{kConvMagic, kStateVersion, conv_hash(g), L.total, g.algo, g.R};
+  L.bf16_weights = g.algo == CO_ALGO_DIRECT && g.dtype == CO_BF16;
+  StateHeader hdr{kConvMagic, kStateVersion, conv_hash(g), L.total, g.algo, g.R,
+                  L.bf16_weights ? kBf16Weights : 0};
   co_conv_handle* h = new (std::nothrow) co_conv_handle{g, L, static_cast<char*>(state), 0};
   if (!h) return CO_EINVAL;
   st = hip_status(launch_conv_init(g, L, h->state, weight, bias, hdr, as_stream(stream)));
@@ -375,7 +385,7 @@ co_status co_conv_init_state_bn(const co_conv_desc* desc, const void* weight, co
   if (g.has_bias && !bias) return CO_EINVAL;
   const ConvLayout L = conv_layout(g);
   if (state_bytes < L.total) return CO_ESTATE;
-  StateHeader hdr{kConvMagic, kStateVersion, conv_hash(g), L.total, g.algo, g.R};
+  StateHeader hdr{kConvMagic, kStateVersion, conv_hash(g), L.total, g.algo, g.R, 0};
   co_conv_handle* h = new (std::nothrow) co_conv_handle{g, L, static_cast<char*>(state), 0};
   if (!h) return CO_EINVAL;
   st = hip_status(launch_conv_init_bn(g, L, h->state, weight, bias, gamma, beta, mean, var, eps,
@@ -535,7 +545,7 @@ co_status co_conv_attach_state(const co_conv_desc* desc, void* state, int64_t st
   ConvGeom g;
   co_status st = conv_geom(desc, &g);
   if (st != CO_OK) return st;
-  const ConvLayout L = conv_layout(g);
+  ConvLayout L = conv_layout(g);
   if (state_bytes < L.total) return CO_ESTATE;
   StateHeader hdr;
   st = read_header(state, as_stream(stream), &hdr);
@@ -543,6 +553,8 @@ co_status co_conv_attach_state(const co_conv_desc* desc, void* state, int64_t st
   if (hdr.magic != kConvMagic || hdr.version != kStateVersion || hdr.desc_hash != conv_hash(g) ||
       hdr.bytes != L.total || hdr.algo != g.algo || hdr.slots != g.R)
     return CO_ESTATE;
+  L.bf16_weights =
+      g.algo == CO_ALGO_DIRECT && g.dtype == CO_BF16 && hdr.weights == kBf16Weights;
   co_conv_handle* h = new (std::nothrow) co_conv_handle{g, L, static_cast<char*>(state), n};
   if (!h) return CO_EINVAL;
   return publish(h, HKind::Conv, out);

@@ -143,6 +143,7 @@ struct ConvLayout {
   int64_t steps_weight, steps_weight_bytes;  // second packing for persistent forward_steps (0: none)
   int64_t ring_slot_elems;  // floats between consecutive ring slots
   int64_t total;
+  int32_t bf16_weights;  // direct: the float32 weights are bf16 values (StateHeader::weights)
 };
 
 struct PoolGeom {
@@ -194,7 +195,11 @@ struct StateHeader {
   int64_t bytes;
   int32_t algo;
   int32_t slots;
+  uint32_t weights;  // kBf16Weights, or anything else (states of earlier versions)
 };
+
+// A direct layer's float32 weights are the caller's bf16 ones, unscaled.
+constexpr uint32_t kBf16Weights = 0x36314642u;  // "BF16"
 
 // Floats in one ring slot: the output frame, padded.
 int64_t ring_slot_elems(const ConvGeom& g);
