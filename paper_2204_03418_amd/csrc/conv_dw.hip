@@ -160,6 +160,7 @@ struct DwSteps {
   int32_t update;   // write the live partial sums back
   int32_t x_bytes, y_bytes;  // buffer extents from the clip pointers
   FastDiv fd_So, fd_Cout, fd_Wo, fd_W;
+  FastDiv fd_pr, fd_pairs, fd_cw;  // output pairs per row and per plane, waves per channel
 };
 
 constexpr int PF = 4;  // frames in flight per thread
@@ -273,6 +274,174 @@ __global__ __launch_bounds__(kBlock) void conv_steps_dw_kernel(
       const int tau = v1 - (KT - 1) + q;
       const int sl = (ds.slot0 + ds.count + q) % KT;
       if (tau >= 0) ring[sl * ring_slot + ridx] = acc[q];
+    }
+  }
+}
+
+// bf16 planes walked in steps of one pixel along a row by 3x3 stencils
+// (sW = dW = 1, W >= 2): a thread owns two neighbouring outputs of a row for
+// the whole clip.  Their stencils cover four columns, loaded as pixel pairs: 6
+// four-byte loads a frame where two threads with an output each took 18
+// two-byte ones.  A pair that reaches over the row's end
+// is loaded one pixel inside, and a byte permute with the lane's own selectors
+// converts each half, picks it from where it landed or makes it zero: the
+// instruction that the conversion takes anyway.  Taps, partial sums and
+// summation order are those of the kernel above.
+//
+// A wave's pairs belong to one channel (of all streams: the ring's order), so
+// the weights are scalar registers and leave the chip full of waves.
+//
+// What bounds it: 27 multiply-adds per output and frame (about 80 vector
+// instructions per pair, 22 us of the 37 in the first measure), then the
+// frames' way from and to memory.  Four outputs a thread save loads but leave
+// rows ragged and half the waves (43 us against 42.5, 14x14 above 56 against
+// 47).  Measured, both ways with the call's own cost: 16 streams, 28x28, 108
+// channels, kT 3, 16 frames 61 -> 42.5 us; 4 streams, 14x14, 432 channels, 64
+// frames 86 -> 47; 16 streams, 56x56, 54 channels, 16 frames 108 -> 76.
+template <int KT>
+__global__ __launch_bounds__(kBlock) void conv_steps_dw2_kernel(
+    ConvGeom g, DwSteps ds, const bf16_t* __restrict__ x, int64_t x_bc, bf16_t* __restrict__ y,
+    int64_t y_bc, const float* __restrict__ w, const float* __restrict__ bias,
+    float* __restrict__ ring, int64_t ring_slot) {
+  constexpr int KH = 3, KW = 3, NS = KH * KW;
+  constexpr int NP = 2;                   // outputs
+  constexpr int NC = KW + NP - 1;         // columns of their stencils
+  constexpr int ND = NC / 2;              // loads per row
+  constexpr int NL = KH * ND;
+  constexpr uint32_t esz = sizeof(bf16_t);
+  const int32_t So = g.Ho * g.Wo;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x) * (kBlock / 64) +
+                                                      int32_t(threadIdx.x >> 6));
+  const int32_t c = fdiv(wave, ds.fd_cw);  // the wave's channel
+  if (c >= g.Cout) return;
+  const int32_t pairs = g.Ho * int32_t(ds.fd_pr.d);  // of a plane
+  const int32_t idx = (wave - c * int32_t(ds.fd_cw.d)) * 64 + (int32_t(threadIdx.x) & 63);
+  if (idx >= g.B * pairs) return;
+  const int32_t bq = fdiv(idx, ds.fd_pairs);
+  const int32_t pp = idx - bq * pairs;
+  const int32_t i = fdiv(pp, ds.fd_pr), jo = NP * (pp - i * int32_t(ds.fd_pr.d));
+  const int32_t p = i * g.Wo + jo;
+  const int32_t left = g.Wo - jo;  // outputs from here on
+  const int32_t bc = bq * g.Cout + c;
+  const int32_t ridx = (c * g.B + bq) * So + p;  // ring (slot, C, B, Ho, Wo)
+
+  float wr[KT][NS];
+#pragma unroll
+  for (int j = 0; j < KT; ++j)
+#pragma unroll
+    for (int e = 0; e < NS; ++e) wr[j][e] = w[(c * KT + j) * NS + e];
+  const float bo = bias[c];
+
+  float acc[KT][NP];
+#pragma unroll
+  for (int q = 0; q < KT; ++q) {
+    const int tau = ds.v0 - (KT - 1) + q;
+    const int sl = (ds.slot0 + q) % KT;
+#pragma unroll
+    for (int h = 0; h < NP; ++h)
+      acc[q][h] = (q < KT - 1 && tau >= 0 && h < left) ? ring[sl * ring_slot + ridx + h] : 0.f;
+  }
+
+  // byte offsets of the loads inside the (b, c) plane of a frame, and how
+  // their halves become columns
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x, ds.x_bytes);
+  const __amdgpu_buffer_rsrc_t yr = make_rsrc(y, ds.y_bytes);
+  const uint32_t plane = uint32_t(bc) * uint32_t(x_bc) * esz;
+  constexpr uint32_t kLow = 0x01000c0cu, kHigh = 0x03020c0cu, kZero = 0x0c0c0c0cu;
+  int32_t soff[NL];
+  uint32_t sel[NC];
+#pragma unroll
+  for (int d = 0; d < ND; ++d) {
+    int32_t col = jo - g.pW + d * 2;
+    const bool in = col >= -1 && col < g.W;
+    sel[2 * d] = col < 0 ? kZero : col == g.W - 1 ? kHigh : kLow;
+    sel[2 * d + 1] = col < 0 ? kLow : col == g.W - 1 ? kZero : kHigh;
+    col = col < 0 ? 0 : col == g.W - 1 ? col - 1 : col;
+#pragma unroll
+    for (int u = 0; u < KH; ++u) {
+      const int32_t hi = i * g.sH + u * g.dH - g.pH;
+      soff[u * ND + d] = in && hi >= 0 && hi < g.H
+                             ? int(plane + uint32_t(hi * g.W + col) * esz)
+                             : kOutOfRange;
+    }
+  }
+  const bool ragged = g.Wo & 1;
+  const int32_t fstride = g.H * g.W * int32_t(esz);  // bytes between frames
+  const int32_t yoff = int32_t((uint32_t(bc) * uint32_t(y_bc) + uint32_t(p)) * esz);
+
+  auto load_frame = [&](int t, uint32_t (&xv)[NL]) __attribute__((always_inline)) {
+    if (t < ds.T) {
+#pragma unroll
+      for (int e = 0; e < NL; ++e)
+        xv[e] = __builtin_amdgcn_raw_buffer_load_b32(xr, soff[e], t * fstride, 0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < NL; ++e) xv[e] = 0u;
+    }
+  };
+  uint32_t xq[PF][NL];  // raw bits, converted when the frame is evaluated
+#pragma unroll
+  for (int u = 0; u < PF; ++u) load_frame(u, xq[u]);
+  for (int t0 = 0; t0 < ds.count; t0 += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      const int t = t0 + u;
+      if (t >= ds.count) break;
+      const int v = ds.v0 + t;
+      float xv[KH][NC];
+#pragma unroll
+      for (int a = 0; a < KH; ++a)
+#pragma unroll
+        for (int b = 0; b < NC; ++b)
+          xv[a][b] = __uint_as_float(__builtin_amdgcn_perm(0u, xq[u][a * ND + b / 2], sel[b]));
+#pragma unroll
+      for (int j = KT - 1; j >= 0; --j) {
+        const int q = KT - 1 - j;
+        const int tau = v - j;
+        const bool exists = tau >= 0;
+        const int first = tau >= g.pT ? 0 : g.pT - tau;  // first tap on a real frame
+        float sum[NP];
+#pragma unroll
+        for (int h = 0; h < NP; ++h) sum[h] = (j == first) ? 0.f : acc[q][h];
+#pragma unroll
+        for (int a = 0; a < KH; ++a)
+#pragma unroll
+          for (int b = 0; b < KW; ++b)
+#pragma unroll
+            for (int h = 0; h < NP; ++h)
+              sum[h] = fmaf(wr[j][a * KW + b], xv[a][b + h], sum[h]);
+        if (j == KT - 1) {
+          const int at = exists ? yoff : kOutOfRange;
+          const int so = exists ? (ds.k0 + t) * So * int32_t(esz) : 0;
+          typedef float v2f __attribute__((ext_vector_type(2)));
+          typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+          const uint32_t pk = __builtin_bit_cast(
+              uint32_t, __builtin_convertvector(v2f{sum[0] + bo, sum[1] + bo}, v2b));
+          __builtin_amdgcn_raw_buffer_store_b32(pk, yr, left >= 2 ? at : kOutOfRange, so, 0);
+          if (ragged)  // uniform: a row ends in a single output
+            store_at(yr, left >= 2 ? kOutOfRange : at, so, bf16_t(pk & 0xffffu));
+        } else {
+#pragma unroll
+          for (int h = 0; h < NP; ++h) acc[q][h] = sum[h];
+        }
+      }
+      // the oldest outputs are complete: shift the others down one place
+#pragma unroll
+      for (int q = 0; q + 1 < KT; ++q)
+#pragma unroll
+        for (int h = 0; h < NP; ++h) acc[q][h] = acc[q + 1][h];
+      load_frame(t + PF, xq[u]);
+    }
+  }
+  if (ds.update) {
+    const int v1 = ds.v0 + ds.count;
+#pragma unroll
+    for (int q = 0; q + 1 < KT; ++q) {
+      const int tau = v1 - (KT - 1) + q;
+      const int sl = (ds.slot0 + ds.count + q) % KT;
+#pragma unroll
+      for (int h = 0; h < NP; ++h)
+        if (tau >= 0 && h < left) ring[sl * ring_slot + ridx + h] = acc[q][h];
     }
   }
 }
@@ -616,6 +785,24 @@ hipError_t dw_steps_launch(const ConvGeom& g, const ConvLayout& L, char* state, 
                        reinterpret_cast<const float*>(state + L.bias),
                        reinterpret_cast<float*>(state + L.ring), L.ring_slot_elems);
     return hipGetLastError();
+  }
+  // two outputs a thread: bf16 only (float32 columns would be loaded and
+  // stored eight bytes apart, 28x28 above 64 -> 82 us), 3x3 stencils (a 1x1
+  // one shares no columns; odd widths 18.4 -> 19.6 us)
+  if constexpr (sizeof(T) == 2 && KW == 3) {
+    if (g.sW == 1 && g.dW == 1 && g.W >= 2) {
+      const int64_t pr = ceil_div(g.Wo, 2), pairs = pr * g.Ho;
+      const int64_t cw = ceil_div(g.B * pairs, 64);
+      ds.fd_pr = make_fastdiv(uint32_t(pr));
+      ds.fd_pairs = make_fastdiv(uint32_t(pairs));
+      ds.fd_cw = make_fastdiv(uint32_t(cw));
+      hipLaunchKernelGGL(conv_steps_dw2_kernel<KT>, dim3(grid_for(cw * g.Cout * 64)),
+                         dim3(kBlock), 0, s, g, ds, static_cast<const T*>(x), x_bc,
+                         static_cast<T*>(y), y_bc, reinterpret_cast<const float*>(state + L.weight),
+                         reinterpret_cast<const float*>(state + L.bias),
+                         reinterpret_cast<float*>(state + L.ring), L.ring_slot_elems);
+      return hipGetLastError();
+    }
   }
   hipLaunchKernelGGL((conv_steps_dw_kernel<T, KH, KW, KT>), dim3(grid_for(g.out_frame_elems())),
                      dim3(kBlock), 0, s, g, ds, static_cast<const T*>(x), x_bc,
