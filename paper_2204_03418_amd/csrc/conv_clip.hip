@@ -91,6 +91,7 @@ struct ClipArgs {
   int32_t tap_bytes;  // (0:) from a tap's last k-step to the next tap's first
   int32_t cgrp, celt;  // channel strides: lane group, element of a 16-byte unit
   int32_t act;
+  int32_t unpadded;  // one spatial tap, no padding: every pixel's lies in its plane
   int32_t win_rows;  // WINDOW: staged pixels, a multiple of 128
   FastDiv fd_nrb, fd_B, fd_nt, fd_So, fd_Wo, fd_R, fd_nq, fd_q, fd_kW, fd_wcols, fd_dT;
 };
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
         fr[i][h] = in ? t0 : kNoFrame;
         const int io = fdiv(p, ca.fd_Wo), jo = p - io * g.Wo;
         const int hi = io * g.sH - g.pH, wi = jo * g.sW - g.pW;
-        if (!PAIR) hw[i] = (hi << 16) | (wi & 0xffff);
+        if (!PAIR) hw[i] = ca.unpadded ? 0 : (hi << 16) | (wi & 0xffff);
         // (of a pair, the first pixel's, or where that has no output the
         // second's less one)
         if (h == 0 || fr[i][0] == kNoFrame) base[i] = t0 * ca.S + hi * g.W + wi - h;
@@ -701,6 +702,9 @@ bool clip_pairs(const ConvGeom& g) {
          g.pH == 0 && g.pW == 0;
 }
 
+// Layers whose one spatial tap never leaves the plane (no bound on its sides).
+bool clip_unpadded(const ConvGeom& g) { return g.kH * g.kW == 1 && g.pH == 0 && g.pW == 0; }
+
 // Workgroups of `tile` channels that `outputs` output frames take.
 int64_t clip_wgs(const ConvGeom& g, int64_t outputs, int tile) {
   return ceil_div(outputs * g.So(), 128) * g.B * ceil_div(g.Cout, tile);
@@ -784,7 +788,8 @@ bool clip_gemm_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames) 
     return false;
   }
   const ConvLayout L = conv_layout(g);
-  return g.G == 1 && g.H < 16384 && g.W < 16384 && g.pH < 8192 && g.pW < 8192 && x_frames >= 1 &&
+  return g.G == 1 &&
+         (clip_unpadded(g) || (g.H < 16384 && g.W < 16384 && g.pH < 8192 && g.pW < 8192)) &&
          int64_t(g.B) * g.Cin * x_frames * g.S() * esz < lim &&
          int64_t(g.B) * g.Cout * y_frames * g.So() * esz < lim &&
          (x_frames + g.f) * g.So() < lim / 4 && int64_t(g.R) * L.ring_slot_elems * 4 < lim &&
@@ -795,32 +800,33 @@ bool clip_gemm_preferred(const ConvGeom& g, int64_t x_frames, bool gemm_steps, b
   // one temporal tap: the frames are independent, a plain GEMM over all of
   // them (4.9x to 2.5x the persistent kernels', 1.3x and more that of two
   // steps)
-  if (g.kT == 1) return x_frames >= 2;
-  if (gemm_steps) {
-    // the persistent 3x3 GEMM walks the frames, about 3.3 us a frame and 32
-    // channels for every 256 workgroups (160 pixels x 64 channels): it keeps
-    // the layers that fill the chip with them
-    GemmStepsConfig c;
-    if (!gemm_steps_config(g, &c) || g.kH * g.kW == 1) return true;
-    const double rounds = double(ceil_div(int64_t(c.m_tiles) * c.o_tiles, 256));
-    return clip_us(g, x_frames) < 8 + x_frames * rounds * c.n_chunks * 3.3;
-  }
-  if (reg_steps) {
-    RegConfig c;
-    if (!reg_config(g, g.cfg, &c)) return false;
-    // 3x3 shapes keep their partial sums and weights in registers
-    if (c.TAPS > 1) return false;
-    // strided or dilated time runs on step plans there: half as fast
-    if (g.sT != 1 || g.dT != 1) return true;
-    const int64_t tiles = int64_t(c.m_frags) * ceil_div(g.Cout, 16);
-    // kT short of the instantiation's taps: every instruction conditional
-    // (2x to 11x).  bf16 with at most 64 channels: the persistent kernel's
-    // eight-wave workgroups win where about a hundred of them share the frames
-    // (32 streams, 64 -> 256, kT 9, 25 joints, 300 frames: 102 us against
-    // 130; 16 streams: 116 us against 81).  fp32: at kT 3 up to 256 tiles
-    // (28 us against 35), at kT 9 never.
-    if (g.dtype == CO_BF16) return !(c.id == 5 && (g.kT == 3 || g.kT == 9) && tiles >= 8 * 90);
-    return !(g.kT == 3 && tiles <= 256);
+  if (g.kT == 1 && (x_frames >= 2 || reg_steps)) return true;
+  GemmStepsConfig sc;
+  RegConfig c;
+  if (gemm_steps_config(g, &sc)) {
+    if (g.kH * g.kW == 1) return true;
+    if (gemm_steps) {
+      // the persistent 3x3 GEMM walks the frames, about 3.3 us a frame and 32
+      // channels for every 256 workgroups (160 pixels x 64 channels): it keeps
+      // the layers that fill the chip with them
+      const double rounds = double(ceil_div(int64_t(sc.m_tiles) * sc.o_tiles, 256));
+      return clip_us(g, x_frames) < 8 + x_frames * rounds * sc.n_chunks * 3.3;
+    }
+  } else if (reg_config(g, g.cfg, &c) && g.algo == CO_ALGO_GEMM_REG) {
+    if (c.TAPS > 1) {
+      // 3x3 shapes keep their partial sums and weights in registers
+      if (reg_steps) return false;
+    } else if (c.id != 7 && g.kT <= (c.id == 1 ? 3 : 9)) {
+      // Persistent kernels at their own kT.  bf16 with at most 64 channels:
+      // their eight-wave workgroups win where about a hundred of them share
+      // the frames (32 streams, 64 -> 256, kT 9, 25 joints, 300 frames: 102 us
+      // against 130; 16 streams: 116 us against 81).  fp32: at kT 3 up to 256
+      // tiles (28 us against 35).  Everything else goes this way: any kT,
+      // stride and dilation (2x to 11x what persistent forms of those took).
+      const int64_t tiles = int64_t(c.m_frags) * ceil_div(g.Cout, 16);
+      if (!reg_steps) return true;
+      return g.dtype == CO_BF16 ? tiles < 8 * 90 : tiles > 256;
+    }
   }
   return clip_us(g, x_frames) < loop_us(g, x_frames);
 }
@@ -884,6 +890,7 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   ca.tap_cols = g.Cout % ca.wcols;
   ca.tap_bytes = int32_t(int64_t(g.Cout / ca.wcols) * ca.wtile - int64_t(ca.nq) * ca.wq);
   ca.act = act;
+  ca.unpadded = clip_unpadded(g);
   ca.fd_B = make_fastdiv(uint32_t(g.B));
   ca.fd_So = make_fastdiv(uint32_t(ca.So));
   ca.fd_Wo = make_fastdiv(uint32_t(g.Wo));

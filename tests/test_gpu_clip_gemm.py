@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from paper_2204_03418_amd import coinf, synth
-from parity_util import oracle_conv, say
+from parity_util import assert_close, conv_terms, np64, oracle_conv, say
 from test_gpu_parity import DEV, _check_fused_steps
 
 pytestmark = pytest.mark.gpu
@@ -65,3 +65,43 @@ def test_clip_gemm_unaligned_clip():
     a, c = (coinf.CoConv(w.to(DEV), b.to(DEV), batch=2, in_size=(5,)) for _ in range(2))
     assert xu.data_ptr() % 4 == 2 and a.steps_fused(31)
     assert torch.equal(a.forward_steps(xu), c.forward_steps(x.to(DEV)))
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[4], CASES[6]], ids=lambda c: c[8] + str(c[4]))
+def test_clip_gemm_end_padding_alone(case):
+    """The end padding in a call of its own, over no frames, gives the outputs
+    that it gives behind the frames."""
+    B, cin, cout, k, size, st, p, dil, dt, T, algo = case
+    say("clip gemm end padding", case)
+    spec = synth.ConvSpec(batch=B, in_channels=cin, out_channels=cout, kernel=k, in_size=size,
+                          stride=st, padding=p, dilation=dil, dtype=dt)
+    x, w, b = synth.conv_inputs(spec, T, 97600, "kaiming")
+    a, c = (coinf.CoConv(w.to(DEV), b.to(DEV), batch=B, in_size=size, stride=st, padding=p,
+                         dilation=dil, algo=algo) for _ in range(2))
+    xd = x.to(DEV)
+    want = a.forward_steps(xd, pad_end=True)
+    head = c.forward_steps(xd)
+    tail = c.forward_steps(xd[:, :, :0].contiguous(), pad_end=True)
+    assert tail is not None and torch.equal(torch.cat([head, tail], 2), want)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_clip_gemm_long_side(dt):
+    """One spatial tap without padding over a plane of 40000 rows, strided in
+    time: the rows are not packed into half words."""
+    say("clip gemm long side", dt)
+    spec = synth.ConvSpec(batch=1, in_channels=33, out_channels=16, kernel=(2, 1),
+                          in_size=(40000,), stride=(2, 1), padding=(0, 0), dtype=dt)
+    x, w, b = synth.conv_inputs(spec, 4, 97700, "kaiming")
+
+    def make():
+        return coinf.CoConv(w.to(DEV), b.to(DEV), batch=1, in_size=(40000,), stride=(2, 1))
+
+    co = make()
+    assert co.steps_fused(4)
+    got = co.forward_steps(x.to(DEV))
+    one = make()
+    steps = [one.forward_step(x[:, :, t].contiguous().to(DEV)) for t in range(4)]
+    assert torch.equal(got, torch.stack([s for s in steps if s is not None], 2))
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), b.double(), stride=(2, 1))
+    assert_close(np64(got), np64(ref), synth.torch_dtype(dt), "long side", terms=conv_terms(w))
