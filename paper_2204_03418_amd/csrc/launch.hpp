@@ -56,8 +56,9 @@ hipError_t launch_pool_step(const PoolGeom& g, const PoolLayout& L, char* state,
 hipError_t launch_pool_init(const PoolGeom& g, const PoolLayout& L, char* state,
                             const StateHeader& hdr, hipStream_t stream);
 
-// Persistent forward_steps of a pool (same conventions as the depthwise one):
-// temporal stride 1 and dilation 1, kT <= 5, a spatial window of at most 64,
+// forward_steps of a pool in one launch (same conventions as the depthwise
+// one): global windows of at most 64 pixels, kT <= 64, spans of at most 128
+// frames; else temporal dilation 1, kT <= 5, a spatial window of at most 64;
 // clips below 2^31 bytes.
 bool pool_steps_supported(const PoolGeom& g, int64_t x_frames, int64_t y_frames);
 // Validity flags of the FIFO slots that pool steps n0 .. n0 + count - 1 wrote
@@ -130,8 +131,9 @@ hipError_t launch_conv_step_gemm(const ConvGeom& g, const ConvLayout& L, char* s
 hipError_t launch_conv_step_reg(const ConvGeom& g, const ConvLayout& L, char* state,
                                 const StepIO& io, const co_step_plan& plan, hipStream_t stream);
 // Persistent forward_steps of the register-GEMM step (same conventions as
-// the depthwise one): temporal stride 1 and dilation 1, kT within what the
-// step kernel's instantiation can hold in registers.
+// the depthwise one): temporal stride and dilation 1, kT within what the
+// step kernel's instantiation can hold in registers (3x3 taps), or a kT at
+// which it beats the GEMM over all frames (one tap).
 bool reg_steps_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames);
 hipError_t launch_conv_steps_reg(const ConvGeom& g, const ConvLayout& L, char* state,
                                  const void* x, int64_t x_bc, int32_t T, int32_t count, void* y,
@@ -139,7 +141,7 @@ hipError_t launch_conv_steps_reg(const ConvGeom& g, const ConvLayout& L, char* s
 hipError_t launch_pack_reg(const ConvGeom& g, const ConvLayout& L, char* state,
                            const void* weight, const float* wscale, hipStream_t stream);
 // Persistent forward_steps of the LDS-tiled GEMM (bf16; same conventions as
-// the depthwise one): temporal stride 1 and dilation 1, kT <= 3, 3x3 or 1x1
+// the depthwise one): temporal stride 1 and dilation 1, kT <= 3, 3x3
 // taps, tiles within the LDS and staging budgets.  x is the clip pointer
 // (pixel pairs must be 4-byte aligned when rows are even).
 bool gemm_steps_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames, const void* x);

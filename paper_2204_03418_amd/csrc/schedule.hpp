@@ -122,8 +122,9 @@ constexpr int64_t kMaxSteps = int64_t(1) << 62;
 // output channels for every temporal tap (N_WG = kStepsKT * O_WG columns),
 // so the partial sums its outputs continue stay in its registers across
 // frames.  Per frame it stages the input in chunks of 32 channels (double
-// buffered) and streams the weights in stages of one chunk x one kernel row
-// (triple buffered).
+// buffered) and streams the weights from L2.  lds_bytes bounds which layers
+// have the second packing, which is part of the state layout: one-tap layers
+// keep its room, unused.
 struct GemmStepsConfig {
   int32_t M_WG, O_WG, N_WG;
   int32_t m_tiles, o_tiles, n_chunks;
