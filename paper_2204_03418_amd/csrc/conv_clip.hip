@@ -89,7 +89,8 @@ struct ClipArgs {
   int32_t wtile;     // bytes between column tiles (or 16-column fragments)
   int32_t tap_cols;  // C_out modulo the column tile
   int32_t tap_bytes;  // (0:) from a tap's last k-step to the next tap's first
-  int32_t cgrp, celt;  // channel strides: lane group, element of a 16-byte unit
+  int32_t cgrp;      // channels between lane groups
+  uint32_t celt;     // bytes between a 16-byte unit's channels (at most 2^31)
   int32_t act;
   int32_t unpadded;  // one spatial tap, no padding: every pixel's lies in its plane
   int32_t win_rows;  // WINDOW: staged pixels, a multiple of 128
@@ -129,7 +130,14 @@ __device__ __forceinline__ void pair_units(const uint32_t (&)[4], uint4&, uint4&
 // alignment) brings a channel of both.  In the second pass they are, too,
 // except where the slots wrap around to the first unfinished output: when that
 // is an odd pixel, the tiles begin one pixel early so that no pair spans it.
-template <typename T, int WMF, int WNF, int NWM, int NWN, bool PAIR, bool WINDOW>
+//
+// FAR: a k-step reaches past C_in by up to its width, and with few channels of
+// many frames those channels' offsets would pass 2^32 and begin again inside
+// the stream, so channel offsets are scalar and stop at the stream's end.  Only
+// for the calls that need it: where few workgroups share the chip, adding the
+// offsets lane by lane is faster (96 -> 96, 3x3x3, 14x14, bf16, 16 frames: 98
+// us against 106; float32 64 -> 64, (9,1), 25 joints: 55.5 against 58).
+template <typename T, int WMF, int WNF, int NWM, int NWN, bool PAIR, bool WINDOW, bool FAR>
 __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 : 3) void conv_clip_gemm_kernel(
     ConvGeom g, ClipArgs ca, const T* __restrict__ x, T* __restrict__ y,
     const uint4* __restrict__ wp, const float* __restrict__ bias, float* __restrict__ ring) {
@@ -147,6 +155,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
   constexpr int NBLK = (4 * MB + NW - 1) / NW;  // pixel blocks a wave stages
   constexpr int esz = int(sizeof(T));
   static_assert(!WINDOW || (PAIR && NW == 4), "window staging");
+  static_assert(!(FAR && PAIR), "channel offsets");
   extern __shared__ uint4 clip_lds[];
   uint4(*As)[M_WG * 4] = reinterpret_cast<uint4(*)[M_WG * 4]>(clip_lds);
 
@@ -167,8 +176,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
   const int m0 = mt * M_WG - ca.shift;  // (the first tile may begin with one pixel too few)
 
   // the stream's planes only: channels past C_in read out of range (zero)
-  const __amdgpu_buffer_rsrc_t xr =
-      make_rsrc(x + int64_t(b) * g.Cin * ca.plane, ((g.Cin - 1) * ca.plane + ca.span) * esz);
+  const int x_bytes = ((g.Cin - 1) * ca.plane + ca.span) * esz;
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x + int64_t(b) * g.Cin * ca.plane, x_bytes);
   const __amdgpu_buffer_rsrc_t yr = make_rsrc(y, ca.y_bytes);
   const __amdgpu_buffer_rsrc_t rr = make_rsrc(ring, ca.ring_bytes);
   const __amdgpu_buffer_rsrc_t br = make_rsrc(bias, g.Cout * 4);
@@ -348,7 +357,6 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
     int rmode[PD][NBLK];
     uint64_t rmoved[PD][NBLK];
     const int lim_c = int(ca.fd_q.d), lim_a = ca.nq / lim_c;
-    const int pb = ca.celt * ca.plane * esz;  // bytes between a unit's channels
     auto forward = [&]() __attribute__((always_inline)) {
       if (++wk.c == lim_c) {
         wk.c = 0;
@@ -402,15 +410,27 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
         const int idx = it * NW + wave;
         const int i = NBLK == 1 ? 0 : it % NBLK;
         const int ch = (ca.tap_outer ? wk.c : wk.a) * CK + (idx & 3) * ca.cgrp;
-        // channels past C_in lie past the stream's planes: zero
-        uint32_t vo = uint32_t(voff[i]) + uint32_t(ch * ca.plane * esz);
+        if constexpr (FAR) {
+          uint32_t co = min(uint32_t(min(ch, g.Cin) * ca.plane) * uint32_t(esz),
+                            uint32_t(x_bytes));
 #pragma unroll
-        for (int e = 0; e < RL; ++e) {
-          if constexpr (esz == 4 || PAIR)
-            raw[slot][it][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, int(vo), 0, 0);
-          else
-            raw[slot][it][e] = __builtin_amdgcn_raw_buffer_load_b16(xr, int(vo), 0, 0);
-          vo += uint32_t(pb);
+          for (int e = 0; e < RL; ++e) {
+            if constexpr (esz == 4)
+              raw[slot][it][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, voff[i], int(co), 0);
+            else
+              raw[slot][it][e] = __builtin_amdgcn_raw_buffer_load_b16(xr, voff[i], int(co), 0);
+            co = min(co + ca.celt, uint32_t(x_bytes));
+          }
+        } else {
+          uint32_t vo = uint32_t(voff[i]) + uint32_t(ch * ca.plane * esz);
+#pragma unroll
+          for (int e = 0; e < RL; ++e) {
+            if constexpr (esz == 4 || PAIR)
+              raw[slot][it][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, int(vo), 0, 0);
+            else
+              raw[slot][it][e] = __builtin_amdgcn_raw_buffer_load_b16(xr, int(vo), 0, 0);
+            vo += ca.celt;
+          }
         }
       }
       forward();
@@ -667,7 +687,8 @@ struct ClipCall {
   hipStream_t s;
 };
 
-template <typename T, int WMF, int WNF, int NWM, int NWN, bool PAIR, bool WINDOW>
+template <typename T, int WMF, int WNF, int NWM, int NWN, bool PAIR, bool WINDOW,
+          bool FAR = false>
 hipError_t clip_launch(ClipCall& c) {
   const ConvGeom& g = *c.g;
   ClipArgs& ca = c.ca;
@@ -680,7 +701,7 @@ hipError_t clip_launch(ClipCall& c) {
   if (blocks == 0) return hipSuccess;
   const size_t stages = size_t(2) * M_WG * 64;
   const size_t window = WINDOW ? size_t(ca.nq) * ca.win_rows * 64 : 0;
-  auto kern = conv_clip_gemm_kernel<T, WMF, WNF, NWM, NWN, PAIR, WINDOW>;
+  auto kern = conv_clip_gemm_kernel<T, WMF, WNF, NWM, NWN, PAIR, WINDOW, FAR>;
   if constexpr (WINDOW) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -867,7 +888,8 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   ca.ntaps = ntaps;
   ca.nq = ntaps * CS;
   ca.cgrp = KL;
-  ca.celt = 1;
+  const int64_t lim = int64_t(1) << 31;
+  ca.celt = uint32_t(x_bc * esz);  // (below 2^31, as C_in planes are)
   if (g.algo == CO_ALGO_GEMM_REG) {
     ca.pack = kPackReg;
     ca.tap_outer = 1;
@@ -876,7 +898,7 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
     ca.wtile = ca.nq * 1024;
     if (g.dtype == CO_F32) {  // word e of lane group q holds channel 4 e + q
       ca.cgrp = 1;
-      ca.celt = 4;
+      ca.celt = uint32_t(std::min(4 * x_bc * esz, lim));
     }
   } else {
     GemmConfig gc;
@@ -901,7 +923,13 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   ca.fd_kW = make_fastdiv(uint32_t(g.kW));
   ca.fd_wcols = make_fastdiv(uint32_t(ca.wcols));
   const int tile = clip_tile(g, ca.E);
-  if (g.dtype == CO_F32) return clip_dispatch<float, false, false>(c, tile);
+  // Where a channel of the last k-step has no 32-bit offset from kOutOfRange
+  // (few channels, long clips): any tile gives the same bits, one is built.
+  const bool far = round_up(g.Cin, 4 * KL) * x_bc * esz > lim;
+  if (g.dtype == CO_F32)
+    return far ? clip_launch<float, 4, 2, 2, 2, false, false, true>(c)
+               : clip_dispatch<float, false, false>(c, tile);
+  if (far) return clip_launch<bf16_t, 4, 2, 2, 2, false, false, true>(c);
   if (!clip_pairs(g) || ca.span < 2) return clip_dispatch<bf16_t, false, false>(c, tile);
   // slots wrap around to output E at the pixel (E mod R) So of a tile row
   ca.shift = ca.tail ? int32_t((int64_t(ca.E % g.R) * ca.So) & 1) : 0;
