@@ -1123,9 +1123,23 @@ static int64_t bneck_frame_bytes(const co_bneck_handle* h) {
   return g.out_frame_elems() * (g.dtype == CO_BF16 ? 2 : 4);
 }
 
-static bool bneck_ws_supported(const co_bneck_handle* h, int32_t frames) {
+static bool bneck_ws_supported(const co_bneck_handle* h, int64_t frames) {
   return clip_gemm_supported(h->pw->g, frames, frames) &&
          convpool_steps_supported(h->dw->g, h->pool->g, frames);
+}
+
+// Frames of a chunk of a call over T of them: as many as a workspace holds and
+// the launches take (their limits bound the frames from above).  Below two: a
+// launch per frame.
+static int32_t bneck_chunk(const co_bneck_handle* h, int32_t T, int64_t workspace_bytes) {
+  const int64_t held = std::min<int64_t>(T, workspace_bytes / bneck_frame_bytes(h));
+  if (held < 2 || bneck_ws_supported(h, held)) return int32_t(std::max<int64_t>(held, 0));
+  int64_t lo = 0, hi = held;  // lo frames are taken (or none are), hi are not
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) / 2;
+    (bneck_ws_supported(h, mid) ? lo : hi) = mid;
+  }
+  return int32_t(lo);
 }
 
 // One fused bottleneck step at the handles' counters, reading input planes
@@ -1172,8 +1186,8 @@ co_status co_bneck_forward_step(co_bneck_handle* h, const void* x_t, void* z_t,
 co_status co_bneck_workspace_bytes(const co_bneck_handle* h, int32_t T, int64_t* bytes) {
   if (!live_bneck(h) || T < 0 || !bytes) return CO_EINVAL;
   const int64_t frame = bneck_frame_bytes(h);
-  const int64_t frames = std::min<int64_t>(T, std::max(kBneckWsBytes / frame, kBneckWsFrames));
-  *bytes = bneck_ws_supported(h, int32_t(frames)) ? frames * frame : 0;
+  const int64_t chunk = bneck_chunk(h, T, std::max(kBneckWsBytes, kBneckWsFrames * frame));
+  *bytes = chunk < 2 ? 0 : chunk * frame;
   return CO_OK;
 }
 
@@ -1211,11 +1225,8 @@ co_status co_bneck_forward_steps_ws(co_bneck_handle* h, const void* x, int32_t T
   // its memory round trip with the next frame's: 64 frames of 16 streams,
   // 192 -> 432 channels, 7x7 took 771 us, and take 76 us this way (31 of them
   // the pointwise GEMM).  A single frame is one fused launch.
-  const int64_t frame = bneck_frame_bytes(h);
-  const int32_t chunk =
-      workspace ? int32_t(std::min<int64_t>(T, workspace_bytes / frame)) : 0;
-  if (chunk >= 2 && (update_state || chunk == T) &&
-      bneck_ws_supported(h, chunk)) {
+  const int32_t chunk = workspace ? bneck_chunk(h, T, workspace_bytes) : 0;
+  if (chunk >= 2 && (update_state || chunk == T)) {
     int64_t k = 0;
     for (int32_t t = 0; t < T; t += chunk) {
       const int32_t n = std::min(chunk, T - t);

@@ -57,3 +57,36 @@ def test_bottleneck_chunks(case, frames):
     assert len(outs) == len(want) == peek.shape[2]
     for i, w in enumerate(want):
         assert torch.equal(outs[i], w) and torch.equal(peek[:, :, i], w)
+
+
+def test_bottleneck_workspace_past_the_launches():
+    """A workspace that holds more frames than one launch addresses (2 GiB of
+    pointwise frames) is used in chunks that a launch takes."""
+    B, ci, co, size, T = 64, 16, 432, (7, 7), 900
+    say("bneck large workspace")
+    x = synth.normal((B, ci, T) + size, 5700, dtype="bf16").to(DEV)
+    w1 = synth.normal((co, ci, 1, 1, 1), 5701, dtype="bf16")
+    w2 = synth.normal((co, 1, 3, 3, 3), 5702, dtype="bf16") * 0.2
+
+    def make():
+        pool = coinf.CoPool("avg", batch=B, channels=co, kernel=(4,) + size, in_size=size,
+                            stride=(1,) + size, dtype=torch.bfloat16)
+        pw = coinf.CoConv(w1.to(DEV), batch=B, in_size=size)
+        dw = coinf.CoConv(w2.to(DEV), batch=B, in_size=size, groups=co, padding=(0, 1, 1))
+        return coinf.Bottleneck(pw, True, dw, True, pool)
+
+    frame = B * co * 49 * 2
+    ws = torch.zeros(T * frame, dtype=torch.uint8, device=DEV)
+    assert ws.numel() > 2 ** 31
+    outs = []
+    for space in (ws, None):
+        bn = make()
+        z = torch.empty((B, co, T, 1, 1), dtype=torch.bfloat16, device=DEV)
+        n = coinf.i32()
+        assert coinf.co_bneck_forward_steps_ws(
+            bn.handle, x.data_ptr(), T, z.data_ptr(), T, 1,
+            None if space is None else space.data_ptr(), 0 if space is None else space.numel(),
+            torch.cuda.current_stream().cuda_stream, ctypes.byref(n)) == coinf.CO_OK
+        outs.append(z[:, :, :n.value])
+    assert bool(ws[:frame].any())
+    assert outs[0].shape[2] > 0 and torch.equal(*outs)
