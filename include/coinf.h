@@ -286,9 +286,10 @@ co_status co_conv_scratch_bytes(int64_t* bytes);
  * output frames: *fused = 1 when the whole call is one kernel launch that
  * keeps the partial sums on chip across frames, 0 when it enqueues one step
  * per frame.  Both give the same outputs, bit for bit.
- * The matrix-core families (register GEMM, GEMM, and direct layers with
- * C_out >= 16 and 64 or more values per temporal tap, groups = 1) run a buffer
- * as one GEMM over its frames for any kT, stride and dilation where that is
+ * The matrix-core families (register GEMM, GEMM, and ungrouped direct layers
+ * with C_out >= 16, at most 31 spatial taps and 64 or more values C_in kH kW
+ * per temporal tap, or 32 and a million multiplications a step; a plain
+ * pointwise layer is not among them) run a buffer as one GEMM over its frames for any kT, stride and dilation where that is
  * faster than stepping (always for one spatial tap), else on a persistent
  * kernel or step by step.  With temporal stride and dilation 1 the depthwise
  * family and small direct layers run fused within their kernels' size limits;

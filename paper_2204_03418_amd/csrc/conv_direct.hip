@@ -555,8 +555,7 @@ hipError_t launch_conv_step(const ConvGeom& g, const ConvLayout& L, char* state,
     case CO_ALGO_GEMM: return launch_conv_step_gemm(g, L, state, io, plan, s);
     case CO_ALGO_GEMM_REG: return launch_conv_step_reg(g, L, state, io, plan, s);
     default:
-      if (direct_mma_layer(g) && direct_mma_fits(g, io.x_bc, 1, io.y_bc))
-        return launch_step_direct_mma(g, L, state, io, plan, s);
+      if (direct_mma_step(g)) return launch_step_direct_mma(g, L, state, io, plan, s);
       return launch_conv_step_direct(g, L, state, io, plan, false, s);
   }
 }

@@ -62,12 +62,15 @@ struct DmArgs {
   int32_t w_bytes, ring_bytes, ring_slot;
   int32_t kt, nq;    // k values and k-steps of a temporal tap
   int32_t khw;       // spatial taps
+  int64_t x_plane, y_plane;  // FAR: elements between input and output channels
   FastDiv fd_nt, fd_B, fd_So, fd_Wo, fd_R, fd_khw, fd_kW, fd_dT;
 };
 
 // BF: bf16 matrix instructions (else float32).  MB: 64-pixel blocks of the
-// workgroup's tile; 2 x 2 waves of 32 MB pixels x 16 WNF channels.
-template <typename T, bool BF, int MB, int WNF>
+// workgroup's tile; 2 x 2 waves of 32 MB pixels x 16 WNF channels.  FAR: one
+// frame whose planes lie past 32-bit offsets of each other (a step on a frame
+// of a large buffer): every channel has a resource of its own.
+template <typename T, bool BF, int MB, int WNF, bool FAR>
 __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_kernel(
     ConvGeom g, DmArgs ca, const T* __restrict__ x, int64_t x_stream, T* __restrict__ y,
     int64_t y_stream, const float* __restrict__ w, const float* __restrict__ bias,
@@ -99,7 +102,8 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
   const int mt = fdiv(pair, ca.fd_B), b = pair - mt * g.B;
   const int m0 = mt * M_WG;
 
-  const __amdgpu_buffer_rsrc_t xr = make_rsrc(x + b * x_stream, ca.x_bytes);
+  const T* xb = x + b * x_stream;
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(xb, ca.x_bytes);
   const __amdgpu_buffer_rsrc_t yr = make_rsrc(y + b * y_stream, ca.y_bytes);
   const __amdgpu_buffer_rsrc_t rr = make_rsrc(ring, ca.ring_bytes);
   const __amdgpu_buffer_rsrc_t wr = make_rsrc(w, ca.w_bytes);
@@ -253,15 +257,18 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
 #pragma unroll
       for (int e = 0; e < KL; ++e) {
         const bool in = k0 + e < ca.kt;
-        const uint32_t off = in ? uint32_t(c * ca.plane + u * g.dH * g.W + v * g.dW) * esz : 0u;
+        const int chan = FAR ? 0 : c * ca.plane;
+        const uint32_t off = in ? uint32_t(chan + u * g.dH * g.W + v * g.dW) * esz : 0u;
         const int sh = in ? 31 - uv : 0;
+        const __amdgpu_buffer_rsrc_t cr =
+            FAR ? make_rsrc(xb + (in ? c : 0) * ca.x_plane, ca.x_bytes) : xr;
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
           const uint32_t vo = ((nm[i] << sh) & 0x80000000u) | (uint32_t(base[i]) + off);
           if constexpr (esz == 2)
-            araw[i][e] = __builtin_amdgcn_raw_buffer_load_b16(xr, int(vo), 0, 0);
+            araw[i][e] = __builtin_amdgcn_raw_buffer_load_b16(cr, int(vo), 0, 0);
           else
-            araw[i][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, int(vo), 0, 0);
+            araw[i][e] = __builtin_amdgcn_raw_buffer_load_b32(cr, int(vo), 0, 0);
         }
         ++uv;
         if (++v == g.kW) {
@@ -375,6 +382,13 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
 #pragma unroll
         for (int f = 0; f < WNF; ++f) {
           const v4f v = acc[mf][f] + v4f{bo[f], bo[f], bo[f], bo[f]};
+          if constexpr (FAR) {
+            T* yo = y + b * y_stream + oc(f) * ca.y_plane + (ca.E * ca.So - left);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (r < left && oc(f) < g.Cout) yo[r] = from_f32<T>(v[r]);
+            continue;
+          }
           const int off = whole && oc(f) < g.Cout ? row[f] + mf * 16 * esz : kOutOfRange;
           if constexpr (esz == 2) {
             typedef uint32_t v2u __attribute__((ext_vector_type(2)));
@@ -447,7 +461,7 @@ struct DmCall {
   hipStream_t s;
 };
 
-template <typename T, bool BF, int MB, int WNF>
+template <typename T, bool BF, int MB, int WNF, bool FAR = false>
 hipError_t dm_launch(DmCall& c) {
   const ConvGeom& g = *c.g;
   DmArgs& ca = c.ca;
@@ -457,7 +471,7 @@ hipError_t dm_launch(DmCall& c) {
   ca.fd_nt = make_fastdiv(uint32_t(ca.n_tiles));
   const int64_t blocks = ceil_div(ca.m_pairs, 8) * 8 * ca.n_tiles;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((conv_direct_mma_kernel<T, BF, MB, WNF>), dim3(unsigned(blocks)), dim3(256),
+  hipLaunchKernelGGL((conv_direct_mma_kernel<T, BF, MB, WNF, FAR>), dim3(unsigned(blocks)), dim3(256),
                      0, c.s, g, ca, static_cast<const T*>(c.x), c.x_stream, static_cast<T*>(c.y),
                      c.y_stream, reinterpret_cast<const float*>(c.state + c.L->weight),
                      reinterpret_cast<const float*>(c.state + c.L->bias),
@@ -466,7 +480,8 @@ hipError_t dm_launch(DmCall& c) {
 }
 
 template <typename T, bool BF>
-hipError_t dm_dispatch(DmCall& c) {
+hipError_t dm_dispatch(DmCall& c, bool far) {
+  if (far) return dm_launch<T, BF, 1, 2, true>(c);  // (the same bits in any tile)
   const int tile = dm_tile(*c.g);
   const bool two = dm_blocks(*c.g, std::max<int64_t>(c.ca.E, c.ca.tail ? c.ca.R : 0), tile) == 2;
   switch (tile) {
@@ -500,6 +515,10 @@ bool direct_mma_fits(const ConvGeom& g, int64_t x_bc, int64_t frames, int64_t y_
   const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
   return frames < (int64_t(1) << 24) && (g.Cin * x_bc + g.S()) * esz < 0x70000000 &&
          g.Cout * y_bc * esz < 0x70000000 && (frames + g.f) * g.So() < (int64_t(1) << 28);
+}
+
+bool direct_mma_step(const ConvGeom& g) {
+  return direct_mma_layer(g) && direct_mma_fits(g, g.S(), 1, g.So());
 }
 
 hipError_t launch_direct_mma(const ConvGeom& g, const ConvLayout& L, char* state, const void* x,
@@ -542,8 +561,15 @@ hipError_t launch_direct_mma(const ConvGeom& g, const ConvLayout& L, char* state
   ca.fd_khw = make_fastdiv(uint32_t(ca.khw));
   ca.fd_kW = make_fastdiv(uint32_t(g.kW));
   ca.fd_dT = make_fastdiv(uint32_t(g.dT));
-  if (g.dtype == CO_F32) return dm_dispatch<float, false>(c);
-  return bf ? dm_dispatch<bf16_t, true>(c) : dm_dispatch<bf16_t, false>(c);
+  const bool far = !direct_mma_fits(g, x_bc, nreal, y_bc);
+  if (far) {  // one frame (launch_step_direct_mma)
+    if (nreal != 1 || !direct_mma_step(g)) return hipErrorInvalidValue;
+    ca.x_bytes = int32_t(g.S() * esz);
+    ca.x_plane = x_bc;
+    ca.y_plane = y_bc;
+  }
+  if (g.dtype == CO_F32) return dm_dispatch<float, false>(c, far);
+  return bf ? dm_dispatch<bf16_t, true>(c, far) : dm_dispatch<bf16_t, false>(c, far);
 }
 
 hipError_t launch_step_direct_mma(const ConvGeom& g, const ConvLayout& L, char* state,

@@ -104,10 +104,13 @@ hipError_t launch_conv_steps_direct(const ConvGeom& g, const ConvLayout& L, char
 // Ungrouped direct layers with enough channels on the matrix cores
 // (conv_direct_mma.hip), one frame or many in a launch, in place of the two
 // kernels above: which layers, whether a call's planes (x_bc, y_bc elements
-// apart) are within its 32-bit offsets (else it steps on the direct kernel),
-// a step, and forward_steps (same conventions as the depthwise one).
+// apart) are within its 32-bit offsets (else it steps), whether the layer's
+// steps run here (wherever their planes lie: the frame's own size decides, so
+// that every step of a layer has the same bits), a step, and forward_steps
+// (same conventions as the depthwise one).
 bool direct_mma_layer(const ConvGeom& g);
 bool direct_mma_fits(const ConvGeom& g, int64_t x_bc, int64_t frames, int64_t y_bc);
+bool direct_mma_step(const ConvGeom& g);
 hipError_t launch_step_direct_mma(const ConvGeom& g, const ConvLayout& L, char* state,
                                   const StepIO& io, const co_step_plan& plan, hipStream_t stream);
 hipError_t launch_direct_mma(const ConvGeom& g, const ConvLayout& L, char* state, const void* x,

@@ -5,6 +5,8 @@ rows of one pixel, both pixel tiles and every channel tile, both dtypes.
 Each against the oracle and bit for bit against single steps, as a clip, as
 the continuation of single steps, before them, and without updating the state.
 """
+import ctypes
+
 import pytest
 import torch
 
@@ -116,3 +118,43 @@ def test_direct_mma_attached_state(marked):
     ref = torch.nn.functional.conv3d(x.double(), w.double(), b.double(), (1, 2, 2), (0, 1, 1))
     assert_close(np64(got), np64(ref[:, :, 1:]), torch.bfloat16, "attached",
                  terms=conv_terms(w))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_direct_mma_buffer_past_32_bits(dt):
+    """A buffer whose planes lie past 32-bit offsets steps frame by frame, with
+    the bits of steps on single frames."""
+    T, hw = (15 if dt == "f32" else 29), 1024
+    say("direct mma large buffer", dt)
+    g = torch.Generator(device=DEV).manual_seed(99500)
+    x = torch.randn((1, 32, T, hw, hw), generator=g, device=DEV).to(synth.torch_dtype(dt))
+    assert 32 * T * hw * hw * x.element_size() >= 0x70000000
+    w = synth.normal((16, 32, 2, 3, 3), 99501, dtype=dt, std=0.1).to(DEV)
+    a, c = (coinf.CoConv(w, batch=1, in_size=(hw, hw), stride=(1, 2, 2), padding=(0, 1, 1),
+                         algo="direct") for _ in range(2))
+    assert not a.steps_fused(T) and a.steps_fused(2)
+    got = a.forward_steps(x)
+    steps = [c.forward_step(x[:, :, t].contiguous()) for t in range(T)]
+    assert torch.equal(got, torch.stack([s for s in steps if s is not None], 2))
+
+
+@pytest.mark.parametrize("scaled", [False, True])
+def test_direct_mma_output_past_32_bits(scaled):
+    """The same of output planes: a small call into a large output buffer."""
+    B, T, cap = 2, 5, 3700000
+    say("direct mma large output", scaled)
+    x = synth.normal((B, 32, T, 7, 8), 99510, dtype="bf16").to(DEV)
+    w = synth.normal((20, 32, 2, 3, 3), 99511, dtype="bf16", std=0.1).to(DEV)
+    bn = tuple(synth.normal((20,), 99512 + i).abs().to(DEV) + 0.5 for i in range(4)) + (1e-5,)
+    a, c = (coinf.CoConv(w, batch=B, in_size=(7, 8), stride=(1, 2, 2), padding=(0, 1, 1),
+                         algo="direct", bn=bn if scaled else None) for _ in range(2))
+    assert 20 * cap * 16 * 2 >= 0x70000000
+    y = torch.zeros((B, 20, cap, 4, 4), dtype=torch.bfloat16, device=DEV)
+    n = coinf.i32()
+    assert coinf.co_conv_forward_steps(a.handle, x.data_ptr(), T, y.data_ptr(), cap, 0, 1,
+                                       torch.cuda.current_stream().cuda_stream,
+                                       ctypes.byref(n)) == coinf.CO_OK
+    steps = [c.forward_step(x[:, :, t].contiguous()) for t in range(T)]
+    want = torch.stack([s for s in steps if s is not None], 2)
+    assert n.value == want.shape[2] and torch.equal(y[:, :, :n.value], want)
+    assert not bool(y[:, :, n.value:n.value + 4].any()) and not bool(y[:, :, -1].any())
