@@ -14,6 +14,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device.hpp"
 #include "launch.hpp"
@@ -386,6 +387,17 @@ __global__ __launch_bounds__(kBlock) void pool_steps_kernel(
 // through 64 launches took 399 us), and as the second half of a bfloat16
 // depthwise + pool clip the whole clip takes 55 us (732 us when each output
 // reduced its own 4 x 49 window).
+//
+// SMALL: planes of at most 16 pixels, in the step kernel's trees of 4 or 16
+// leaves (the others are neutral) and with as few staging loads.  SPLIT: the
+// calls whose work the form above leaves on too few lanes or CUs.  Calls of at
+// most 32 frames take several planes in a pass (lane (pl, tl) is frame tl of
+// plane pl): of many planes a block of 64 lanes for each plane costs what 64
+// frames cost (65536 planes, two frames, kT 4: 1x1 float32 55 us in one form for
+// all, 14 on lane groups, 9.7 here; 8x8 bf16 72, 47 and 9.6).  Clips of few planes
+// are cut along time, each piece beginning with the blocks that its windows
+// reach back to: one workgroup walks 64 frames in 1.3 to 2 us (one plane, 7x7,
+// 20000 frames, kT 4: 613 us in one piece, 35 with a thread per output, 10.6 here).
 constexpr int kPgFrames = 64;  // frames per block, one per lane
 constexpr int kPgWaves = 4;
 constexpr int kPgMaxSpan = 128;  // window span f the LDS history is sized for
@@ -405,13 +417,25 @@ struct PoolGlobalArgs {
   FastDiv fd_F, fd_sT;
 };
 
-template <typename T, int KTB, bool IS_MAX>
+// Split calls.  (A struct of its own: with more arguments, the other form is
+// given other registers and measured up to 5% slower.)
+struct PoolSplitArgs : PoolGlobalArgs {
+  int32_t seg;        // blocks per workgroup (clips: segments of the time axis)
+  int32_t warm;       // blocks whose frames reach into the next block's windows
+  int32_t pp;         // planes in one pass (short calls)
+  int32_t tshift;     // log2 of a plane's lanes: pp << tshift = 64
+  int32_t hlen;       // history entries of a plane
+};
+
+template <typename T, int KTB, bool IS_MAX, bool SMALL, bool SPLIT>
 __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
-    PoolGeom g, PoolGlobalArgs pa, const T* __restrict__ x, int64_t x_bc, T* __restrict__ y,
-    int64_t y_bc, float* __restrict__ fifo, int64_t fifo_slot, float* __restrict__ valid) {
+    PoolGeom g, typename std::conditional<SPLIT, PoolSplitArgs, PoolGlobalArgs>::type pa,
+    const T* __restrict__ x, int64_t x_bc, T* __restrict__ y, int64_t y_bc,
+    float* __restrict__ fifo, int64_t fifo_slot, float* __restrict__ valid) {
   extern __shared__ uint4 pg_lds[];
   constexpr uint32_t esz = sizeof(T);
-  constexpr int NU = esz == 2 ? 9 : 17;  // 16-byte units per lane and block
+  // 16-byte units per lane and block
+  constexpr int NU = (SMALL ? 16 : 64) * int(esz) / 16 + 1;
   constexpr bool is_max = IS_MAX;
   const float neutral = is_max ? -INFINITY : 0.f;
   const int tid = int(threadIdx.x);
@@ -424,7 +448,20 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
   const bool counted = !is_max && !g.count_include_pad;
   char* lds = reinterpret_cast<char*>(pg_lds);
   char* stage = lds + wave * pa.stage;
-  const int hlen = F - 1 + kPgFrames;
+  int pp = 1, pl = 0, tl = lane, hlen = F - 1 + kPgFrames;
+  int b_out = 0, b_lo = 0, b_hi = pa.nblk;
+  if constexpr (SPLIT) {
+    // this lane's plane of a pass and frame of a block
+    pp = pa.pp;
+    pl = lane >> pa.tshift;
+    tl = lane & ((1 << pa.tshift) - 1);
+    hlen = pa.hlen;
+    // this workgroup's blocks: a later segment of a clip first runs through the
+    // blocks that its windows reach back to, without emitting
+    b_out = int(blockIdx.y) * pa.seg;
+    b_lo = max(0, b_out - pa.warm);
+    b_hi = min(pa.nblk, b_out + pa.seg);
+  }
   float* hist = reinterpret_cast<float*>(lds + kPgWaves * pa.stage);
   float* okay = hist + per * hlen;  // the history's flags, alike for all planes
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(x, pa.x_bytes);
@@ -446,7 +483,12 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
     }
   __syncthreads();
 
-  // block b of local plane q: its real frames in 16-byte units from the
+  const int q0 = wave * pa.ppw;
+  const int nq = min(pa.ppw, pa.planes - bc0 - q0);  // this wave's planes (<= 0: none)
+  auto planes_of = [&](int q) { return min(pp, q0 + nq - q); };
+
+  // block b of local plane q, or all the frames of the pp planes from q on
+  // (they lie side by side): its real frames in 16-byte units from the
   // 16-byte boundary at or below their first byte; units past them read the
   // out-of-range offset.  A last unit that would run past the clip's end is
   // left to `tail` single elements, read when the block is staged (once a call)
@@ -456,7 +498,8 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
   auto block = [&](int q, int b) {
     Block k;
     const int t0 = b * kPgFrames;
-    const int nr = min(max(pa.T - t0, 0), kPgFrames);
+    const int nr =
+        pp > 1 ? planes_of(q) * pa.T : min(max(pa.T - t0, 0), kPgFrames);
     k.s0 = int(uint32_t(bc0 + q) * uint32_t(x_bc) * esz) + t0 * pa.fstride;
     k.a0 = k.s0 & ~15;
     const int bytes = nr > 0 ? k.s0 + nr * pa.fstride - k.a0 : 0;
@@ -482,16 +525,15 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
   };
   auto comb = [&](float a, float c) { return is_max ? fmaxf(a, c) : a + c; };
 
-  const int q0 = wave * pa.ppw;
-  const int nq = min(pa.ppw, pa.planes - bc0 - q0);  // this wave's planes (<= 0: none)
   uint4 v[NU];
-  Block cb = block(q0, 0);
+  Block cb = block(q0, b_lo);
   if (nq <= 0) cb.units = cb.tail = 0;
   fetch(cb, v);
-  for (int q = q0; q < q0 + nq; ++q) {
-    float* hq = hist + q * hlen;
-    const int yplane = int(uint32_t(bc0 + q) * uint32_t(y_bc) * esz);
-    for (int b = 0; b < pa.nblk; ++b) {
+  for (int q = q0; q < q0 + nq; q += pp) {
+    const bool mine = !SPLIT || pl < planes_of(q);
+    float* hq = hist + (mine ? q + pl : q) * hlen;
+    const int yplane = int(uint32_t(bc0 + q + pl) * uint32_t(y_bc) * esz);
+    for (int b = b_lo; b < b_hi; ++b) {
 #pragma unroll
       for (int j = 0; j < NU; ++j)
         if (j * 64 + lane < cb.units) reinterpret_cast<uint4*>(stage)[j * 64 + lane] = v[j];
@@ -506,22 +548,22 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
       }
       order();
       const int shift = cb.s0 - cb.a0;
-      const bool more = b + 1 < pa.nblk;
-      if (more || q + 1 < q0 + nq) {
-        cb = more ? block(q, b + 1) : block(q + 1, 0);
+      const bool more = b + 1 < b_hi;
+      if (more || q + pp < q0 + nq) {
+        cb = more ? block(q, b + 1) : block(q + pp, b_lo);
         fetch(cb, v);
       }
 
-      // lane t: frame t0 + t, its S elements in leaves 0..S-1.  The leaf
+      // lane (pl, tl): frame t0 + tl, its S elements in leaves 0..S-1.  The leaf
       // masks are built from a vector copy of S made here, in the loop: as
       // loop invariants the compiler would hoist all 64 of them, as scalar
       // lane masks, out of the loop and spill them
       int Sv;
       __asm__ volatile("v_mov_b32 %0, %1" : "=v"(Sv) : "s"(S));
       const uint32_t nb = __float_as_uint(neutral);
-      const int t = b * kPgFrames + lane;
-      const bool real = t < pa.T;
-      const char* fb = stage + shift + (real ? lane : 0) * pa.fstride;
+      const int t = b * kPgFrames + tl;
+      const bool real = (t < pa.T) & mine;
+      const char* fb = stage + shift + (real ? pl * pa.T + tl : 0) * pa.fstride;
       auto leaf = [&](int r) {
         float xv;
         if constexpr (esz == 2)
@@ -533,19 +575,39 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
         const uint32_t keep = uint32_t((r - Sv) >> 31);  // all ones when r < S
         return __uint_as_float((__float_as_uint(lv) & keep) | (nb & ~keep));
       };
-      float tr[32];
-      if (S > 32) {  // uniform
+      // the tree of the step kernel's lane group; leaves past the smallest
+      // group that holds S are neutral and left out
+      float red;
+      auto tree = [&](auto& tr) __attribute__((always_inline)) {
+        constexpr int n = int(sizeof(tr) / sizeof(float));
 #pragma unroll
-        for (int l = 0; l < 32; ++l) tr[l] = comb(leaf(l), leaf(l + 32));
+        for (int m = n / 2; m > 0; m >>= 1)
+#pragma unroll
+          for (int l = 0; l < m; ++l) tr[l] = comb(tr[l], tr[l + m]);
+        red = tr[0];
+      };
+      if constexpr (!SMALL) {
+        float tr[32];
+        if (S > 32) {  // uniform
+#pragma unroll
+          for (int l = 0; l < 32; ++l) tr[l] = comb(leaf(l), leaf(l + 32));
+        } else {
+#pragma unroll
+          for (int l = 0; l < 32; ++l) tr[l] = leaf(l);
+        }
+        tree(tr);
+      } else if (S > 4) {  // uniform
+        float tr[16];
+#pragma unroll
+        for (int l = 0; l < 16; ++l) tr[l] = leaf(l);
+        tree(tr);
       } else {
+        float tr[4];
 #pragma unroll
-        for (int l = 0; l < 32; ++l) tr[l] = leaf(l);
+        for (int l = 0; l < 4; ++l) tr[l] = leaf(l);
+        tree(tr);
       }
-#pragma unroll
-      for (int m = 16; m > 0; m >>= 1)
-#pragma unroll
-        for (int l = 0; l < m; ++l) tr[l] = comb(tr[l], tr[l + m]);
-      hq[F - 1 + lane] = real ? tr[0] : neutral;
+      if (mine) hq[F - 1 + tl] = real ? red : neutral;
       order();
 
       // the window of frame t: history entries t0 + t + q dT of the block
@@ -556,7 +618,7 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
 #pragma unroll
       for (int a = 0; a < KTB; ++a) {
         tv[a] = neutral;
-        if (a < kTs) tv[a] = hq[lane + a * dT];  // uniform
+        if (a < kTs) tv[a] = hq[tl + a * dT];  // uniform
       }
 #pragma unroll
       for (int m = KTB / 2; m > 0; m >>= 1)
@@ -568,7 +630,7 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
         if (counted) {
           float cnt = 0.f;  // whole numbers: any order
           for (int a = 0; a < kT; ++a) {
-            const int e = b * kPgFrames + lane + a * dT - (F - 1);  // frame of the call
+            const int e = b * kPgFrames + tl + a * dT - (F - 1);  // frame of the call
             cnt += e < 0 ? okay[F - 1 + e] : e < pa.T ? 1.f : 0.f;
           }
           div = cnt * float(S);
@@ -577,10 +639,13 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
       }
       const int te = t - pa.t_e0;
       const int k = te >= 0 ? fdiv(te, pa.fd_sT) : 0;  // the call's k-th output
-      const bool emits = t < pa.count && te >= 0 && te == k * g.sT;
+      const bool emits =
+          mine && (!SPLIT || b >= b_out) && t < pa.count && te >= 0 && te == k * g.sT;
       store_at(yr, emits ? yplane + k * int(esz) : kOutOfRange, 0, from_f32<T>(out));
 
-      // the span before the next block: the block's last F - 1 frames
+      // the span before the next block: the block's last F - 1 frames (a pass
+      // over several planes is the call's only one: its span stays in place)
+      if (pp > 1) break;
       const int nf = min(kPgFrames, pa.count - b * kPgFrames);
       for (int i0 = 0; i0 < F - 1; i0 += 64) {
         const int i = i0 + lane;
@@ -596,11 +661,12 @@ __global__ __launch_bounds__(64 * kPgWaves) void pool_steps_global_kernel(
   // the call's last F - 1 frames go to their FIFO slots: history entry i is
   // frame n0 + count - (F - 1) + i
   const int first = max(0, F - 1 - pa.count);
+  const int at = pp > 1 ? pa.count : 0;
   for (int e = first * per + tid; e < (F - 1) * per; e += 64 * kPgWaves) {
     const int i = e / per, q = e - i * per;
     const int v = pa.slot0 + pa.count + 1 + i;
     const int slot = v - fdiv(v, pa.fd_F) * F;
-    if (bc0 + q < pa.planes) fifo[int64_t(slot) * fifo_slot + bc0 + q] = hist[q * hlen + i];
+    if (bc0 + q < pa.planes) fifo[int64_t(slot) * fifo_slot + bc0 + q] = hist[q * hlen + at + i];
   }
   // nobody reads the flags of this layer in this launch (otherwise they are
   // written by a launch of their own)
@@ -676,22 +742,50 @@ bool pool_global_fits(const PoolGeom& g) {
          g.H * g.W <= 64 && g.kT <= 64 && g.f <= kPgMaxSpan;
 }
 
+template <typename T, bool IS_MAX, bool SMALL>
+auto pool_global_pick(int kT) {
+  return kT <= 8    ? pool_steps_global_kernel<T, 8, IS_MAX, SMALL, false>
+         : kT <= 16 ? pool_steps_global_kernel<T, 16, IS_MAX, SMALL, false>
+         : kT <= 32 ? pool_steps_global_kernel<T, 32, IS_MAX, SMALL, false>
+                    : pool_steps_global_kernel<T, 64, IS_MAX, SMALL, false>;
+}
+
+// Split calls come with the smallest and the largest temporal tree only.
+template <typename T, bool IS_MAX, bool SMALL>
+auto pool_split_pick(int kT) {
+  return kT <= 8 ? pool_steps_global_kernel<T, 8, IS_MAX, SMALL, true>
+                 : pool_steps_global_kernel<T, 64, IS_MAX, SMALL, true>;
+}
+
 // state null: clip mode (a stream that begins and ends with the clip).
-template <typename T, int KTB>
-hipError_t pool_global_launch(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
-                              int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
-                              int64_t n0, bool update, hipStream_t s) {
+template <typename T>
+hipError_t pool_global_t(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
+                         int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
+                         int64_t n0, bool update, hipStream_t s) {
   const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
-  PoolGlobalArgs pa;
+  PoolSplitArgs pa;
   pa.T = nreal;
   pa.count = count;
   pa.nblk = int32_t((int64_t(count) + kPgFrames - 1) / kPgFrames);
   pa.planes = int32_t(int64_t(g.B) * g.C);
+  pa.F = g.f;
+  // short calls: as many planes in a pass as have frames for the lanes (they
+  // are staged in one run)
+  pa.tshift = 6;
+  pa.pp = 1;
+  while (pa.tshift > 0 && 1 << (pa.tshift - 1) >= count && x_bc == nreal * g.S()) {
+    --pa.tshift;
+    pa.pp *= 2;
+  }
   // planes per wave: runs of 16 planes of the FIFO per workgroup where that
   // leaves a workgroup per CU, else more workgroups
-  pa.ppw = 4;
+  pa.ppw = std::max(4, pa.pp);
   while (pa.ppw > 1 && pa.planes / (kPgWaves * pa.ppw) < 256) pa.ppw /= 2;
-  pa.F = g.f;
+  if (pa.pp > pa.ppw) {
+    pa.pp = pa.ppw;
+    pa.tshift = 6 - __builtin_ctz(unsigned(pa.pp));
+  }
+  pa.hlen = pa.F - 1 + (1 << pa.tshift);
   pa.hist0 = int32_t(std::max<int64_t>(0, g.f - 1 - n0));
   pa.slot0 = int32_t(n0 % g.f);
   const int64_t te = n0 >= g.d ? (g.sT - (n0 - g.d) % g.sT) % g.sT : g.d - n0;
@@ -703,38 +797,50 @@ hipError_t pool_global_launch(const PoolGeom& g, const PoolLayout& L, char* stat
   pa.fd_F = make_fastdiv(uint32_t(g.f));
   pa.fd_sT = make_fastdiv(uint32_t(g.sT));
   // a block, its alignment shift and the 64-element over-read of the last lane
-  const int64_t rows = std::min<int64_t>(kPgFrames, nreal);
+  const int64_t rows = std::min<int64_t>(kPgFrames, int64_t(nreal) * pa.pp);
   pa.stage = int32_t(((rows * g.S() + 64) * esz + 32 + 15) / 16 * 16);
   const int per = kPgWaves * pa.ppw;
-  const int lds = kPgWaves * pa.stage + (per * (pa.F - 1 + kPgFrames) + pa.F) * 4;
+  const int lds = kPgWaves * pa.stage + (per * pa.hlen + pa.F) * 4;
+  // a clip has no FIFO: where its planes leave CUs without work, its blocks go
+  // to several workgroups, each at least twice as long as its warm-up
+  const int64_t wgs = (int64_t(pa.planes) + per - 1) / per;
+  pa.warm = (pa.F - 1 + kPgFrames - 1) / kPgFrames;
+  int64_t segs = 1;
+  if (!state)
+    segs = std::max<int64_t>(1, std::min<int64_t>(1024 / wgs, pa.nblk / std::max(1, 2 * pa.warm)));
+  pa.seg = int32_t((pa.nblk + segs - 1) / segs);
+  segs = (pa.nblk + pa.seg - 1) / std::max(pa.seg, 1);
   float* fifo = state ? reinterpret_cast<float*>(state + L.fifo) : nullptr;
   float* valid = state ? reinterpret_cast<float*>(state + L.valid) : nullptr;
-  auto kern = g.kind == CO_POOL_MAX ? pool_steps_global_kernel<T, KTB, true>
-                                     : pool_steps_global_kernel<T, KTB, false>;
-  if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, dim3(unsigned((int64_t(pa.planes) + per - 1) / per)),
-                     dim3(64 * kPgWaves), lds, s, g, pa, static_cast<const T*>(x), x_bc,
-                     static_cast<T*>(y), y_bc, fifo, L.fifo_slot_elems, valid);
-  hipError_t e = hipGetLastError();
+  const bool small = g.S() <= 16, max = g.kind == CO_POOL_MAX;
+  auto launch = [&](auto kern, const auto& args) {
+    if (lds > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(unsigned(wgs), unsigned(std::max<int64_t>(segs, 1))),
+                       dim3(64 * kPgWaves), lds, s, g, args, static_cast<const T*>(x), x_bc,
+                       static_cast<T*>(y), y_bc, fifo, L.fifo_slot_elems, valid);
+    return hipGetLastError();
+  };
+  hipError_t e;
+  if (pa.pp > 1 || segs > 1)
+    e = launch(max && small ? pool_split_pick<T, true, true>(g.kT)
+               : max        ? pool_split_pick<T, true, false>(g.kT)
+               : small      ? pool_split_pick<T, false, true>(g.kT)
+                            : pool_split_pick<T, false, false>(g.kT),
+               pa);
+  else
+    e = launch(max && small ? pool_global_pick<T, true, true>(g.kT)
+               : max        ? pool_global_pick<T, true, false>(g.kT)
+               : small      ? pool_global_pick<T, false, true>(g.kT)
+                            : pool_global_pick<T, false, false>(g.kT),
+               static_cast<const PoolGlobalArgs&>(pa));
   if (e != hipSuccess || !pa.update) return e;
   if (g.kind == CO_POOL_MAX || g.count_include_pad) return e;  // written in the launch
   hipLaunchKernelGGL(pool_valid_kernel, dim3(1), dim3(64), 0, s, valid, g.R, n0, count, nreal);
   return hipGetLastError();
-}
-
-template <typename T>
-hipError_t pool_global_t(const PoolGeom& g, const PoolLayout& L, char* state, const void* x,
-                         int64_t x_bc, int32_t nreal, int32_t count, void* y, int64_t y_bc,
-                         int64_t n0, bool update, hipStream_t s) {
-  const auto launch = g.kT <= 8    ? pool_global_launch<T, 8>
-                      : g.kT <= 16 ? pool_global_launch<T, 16>
-                      : g.kT <= 32 ? pool_global_launch<T, 32>
-                                   : pool_global_launch<T, 64>;
-  return launch(g, L, state, x, x_bc, nreal, count, y, y_bc, n0, update, s);
 }
 
 template <typename T, int G, int KT>
@@ -831,7 +937,14 @@ hipError_t launch_pool_clip(const PoolGeom& g, int32_t T, int32_t T_out, const v
   // a clip is a stream that begins with it and ends with its end padding
   // (Principles 2 and 4), so the frames-in-lanes kernel serves it without a
   // state; other windows reduce every output's window on its own
-  if (pool_global_fits(g) && pool_steps_supported(g, T, T_out)) {
+  // A window over single pixels is kT values, and threads beside each other read
+  // values beside each other: for a few of them and a million outputs a thread
+  // per output is the faster (16 x 432 planes, float32: 2000 frames, kT 1 51 us
+  // against 70, kT 4 84 against 78; 300 frames, kT 4 14.6 against 16.7, kT 16
+  // 31 against 26; 432 planes of 2000 frames 9.6 against 9).
+  const bool single =
+      g.S() == 1 && g.kT <= (T < 1024 ? 4 : 2) && total >= (int64_t(1) << 20);
+  if (!single && pool_global_fits(g) && pool_steps_supported(g, T, T_out)) {
     const auto launch = g.dtype == CO_BF16 ? pool_global_t<bf16_t> : pool_global_t<float>;
     return launch(g, PoolLayout{}, nullptr, x, int64_t(T) * g.S(), T, T + g.pT, y,
                   int64_t(T_out), 0, false, s);

@@ -65,3 +65,23 @@ def test_frames_in_lanes_pool(case):
     assert len(parts) == len(seq)
     for g_, s_ in zip(parts, seq):
         assert torch.equal(g_, s_)
+
+
+FORMS = [
+    # short calls of many planes: several planes in a pass, ragged last ones
+    ("avg", 8, 2050, 8, 4, (2, 2), 1, 0, 1, True, "f32"),
+    ("max", 4, 4100, 9, 3, (1, 3), 2, 1, 2, True, "bf16"),
+    ("avg", 2, 8200, 8, 4, (4, 4), 1, 1, 1, False, "bf16"),
+    ("avg", 1, 16500, 21, 9, (5, 5), 1, 4, 1, False, "f32"),
+    # long clips of few planes: segments of the time axis, with and without
+    # blocks before them that their windows reach back to
+    ("max", 1, 3, 1500, 64, (3, 3), 1, 32, 2, True, "f32"),
+    ("avg", 1, 2, 1300, 40, (4, 4), 1, 20, 1, False, "bf16"),
+    ("max", 1, 2, 700, 5, (7, 7), 3, 2, 1, True, "bf16"),
+    ("avg", 1, 1, 900, 1, (1, 1), 1, 0, 1, True, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", FORMS, ids=lambda c: "_".join(map(str, c[:5])))
+def test_frames_in_lanes_pool_forms(case):
+    test_frames_in_lanes_pool(case)
