@@ -286,20 +286,36 @@ co_status co_conv_scratch_bytes(int64_t* bytes);
  * output frames: *fused = 1 when the whole call is one kernel launch that
  * keeps the partial sums on chip across frames, 0 when it enqueues one step
  * per frame.  Both give the same outputs, bit for bit.
- * The matrix-core families (register GEMM, GEMM, and ungrouped direct layers
- * with C_out >= 16, at most 31 spatial taps and 64 or more values C_in kH kW
- * per temporal tap, or 32 and a million multiplications a step; a plain
- * pointwise layer is not among them) run a buffer as one GEMM over its frames for any kT, stride and dilation where that is
- * faster than stepping (always for one spatial tap), else on a persistent
- * kernel or step by step.  With temporal stride and dilation 1 the depthwise
- * family and small direct layers run fused within their kernels' size limits;
- * with a stride or dilation above 1 (Principle 5) the depthwise family on
- * planes of at most 64 pixels and small direct layers do, following the step
- * plans, when the ring has at most 8 slots, kT <= 10, sT R <= 64 and
- * (kT - 1) dT <= 32.  Host-only.
+ * The matrix-core families (register GEMM, GEMM) run a call the way that is
+ * estimated to be fastest for its size: as one GEMM over its frames (any kT,
+ * stride and dilation), as one persistent launch where a kernel takes the
+ * layer, or step by step, which short calls are.  Ungrouped direct layers with
+ * C_out >= 16, at most 31 spatial taps and 64 or more values C_in kH kW per
+ * temporal tap, or 32 and a million multiplications a step (a plain pointwise
+ * layer is not among them) run as one GEMM over their frames.  With temporal
+ * stride and dilation 1 the depthwise family and small direct layers run fused
+ * within their kernels' size limits; with a stride or dilation above 1
+ * (Principle 5) the depthwise family on planes of at most 64 pixels and small
+ * direct layers do, following the step plans, when the ring has at most 8
+ * slots, kT <= 10, sT R <= 64 and (kT - 1) dT <= 32.  Host-only.
  */
 co_status co_conv_steps_fused(const co_conv_handle* h, int32_t T, int32_t y_cap_frames,
                               int32_t* fused);
+
+/*
+ * Which way that is, from the layer alone: CO_STEPS_LOOP, or the kernel of the
+ * one launch (a call without scratch for its loop, and clip mode, which leaves
+ * no state, may take another way).  Host-only.
+ */
+#define CO_STEPS_LOOP        0  /* a launch per frame */
+#define CO_STEPS_DEPTHWISE   1  /* persistent depthwise kernel */
+#define CO_STEPS_DIRECT_MMA  2  /* GEMM over the frames, direct layers */
+#define CO_STEPS_DIRECT      3  /* persistent direct kernel */
+#define CO_STEPS_GEMM        4  /* persistent LDS-tiled GEMM */
+#define CO_STEPS_REG         5  /* persistent register GEMM */
+#define CO_STEPS_CLIP        6  /* GEMM over the frames, GEMM families */
+co_status co_conv_steps_route(const co_conv_desc* desc, int32_t T, int32_t y_cap_frames,
+                              int32_t update_state, int32_t* route);
 
 /*
  * forward (Principle 2, clip mode): the regular convolution of the clip

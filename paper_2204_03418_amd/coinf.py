@@ -105,6 +105,7 @@ co_conv_attach_state = _sig("co_conv_attach_state", i32, [CD, vp, i64, i64, vp, 
 co_conv_destroy = _sig("co_conv_destroy", i32, [vp])
 co_conv_algo_name = _sig("co_conv_algo_name", ctypes.c_char_p, [vp])
 co_conv_steps_fused = _sig("co_conv_steps_fused", i32, [vp, i32, i32, pi32])
+co_conv_steps_route = _sig("co_conv_steps_route", i32, [CD, i32, i32, i32, pi32])
 co_conv_forward_steps_noalloc = _sig("co_conv_forward_steps_noalloc", i32,
                                      [vp, vp, i32, vp, i32, i32, i32, vp, pi32])
 co_conv_scratch_bytes = _sig("co_conv_scratch_bytes", i32, [pi64])
@@ -423,11 +424,15 @@ class CoConv:
         return conv_out_frames(self.desc, self.steps, T, pad_end)
 
     def steps_fused(self, T, pad_end=False):
-        """True when forward_steps over T frames runs as one persistent launch."""
+        """True when forward_steps over T frames runs as one launch."""
         f = i32()
         check(co_conv_steps_fused(self.handle, T, self.out_frames(T, pad_end), ctypes.byref(f)),
               "co_conv_steps_fused")
         return bool(f.value)
+
+    def steps_route(self, T, pad_end=False, update_state=True):
+        """How forward_steps over T frames runs (STEPS_ROUTES)."""
+        return conv_steps_route(self.desc, T, self.out_frames(T, pad_end), update_state)
 
     def folded(self):
         """(weight, bias) with the batch normalisation folded in, in the io
@@ -452,6 +457,17 @@ class CoConv:
 
     def clean_state(self):
         check(co_conv_clean_state(self.handle, _stream()), "co_conv_clean_state")
+
+
+STEPS_ROUTES = ("loop", "depthwise", "direct_mma", "direct", "gemm", "reg", "clip")
+
+
+def conv_steps_route(desc, T, y_cap_frames, update_state=True):
+    """How forward_steps over T frames of such a layer runs (co_conv_steps_route)."""
+    r = i32()
+    check(co_conv_steps_route(ctypes.byref(desc), T, y_cap_frames, 1 if update_state else 0,
+                              ctypes.byref(r)), "co_conv_steps_route")
+    return STEPS_ROUTES[r.value]
 
 
 def conv_out_frames(desc, n0, T, pad_end=False):

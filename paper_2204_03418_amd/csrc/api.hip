@@ -168,27 +168,26 @@ struct Scratch {
   int64_t bytes;
 };
 
-// How a forward_steps call over T frames of clip x runs: as one launch of a
-// family's persistent kernel or of the clip GEMM, or as a loop of steps.
-enum class StepsRoute { Loop, Depthwise, DirectMma, Direct, Gemm, Reg, Clip };
-
-StepsRoute steps_route(const ConvGeom& g, int32_t T, int32_t y_cap_frames, const void* x) {
+// How a forward_steps call over T frames of clip x runs, `count` with its end
+// padding.
+StepsRoute steps_route(const ConvGeom& g, int32_t T, int64_t count, int32_t y_cap_frames,
+                       const void* x, StepsMode mode) {
   if (dw_steps_supported(g, T, y_cap_frames)) return StepsRoute::Depthwise;
   if (direct_mma_layer(g))
     return direct_mma_fits(g, int64_t(T) * g.S(), T, int64_t(y_cap_frames) * g.So())
                ? StepsRoute::DirectMma
                : StepsRoute::Loop;
   if (direct_steps_supported(g, T, y_cap_frames)) return StepsRoute::Direct;
-  const bool gemm = gemm_steps_supported(g, T, y_cap_frames, x);
-  const bool reg = reg_steps_supported(g, T, y_cap_frames);
-  if (clip_gemm_supported(g, T, y_cap_frames) && clip_gemm_preferred(g, T, gemm, reg))
-    return StepsRoute::Clip;
-  return gemm ? StepsRoute::Gemm : reg ? StepsRoute::Reg : StepsRoute::Loop;
+  if (g.algo != CO_ALGO_GEMM && g.algo != CO_ALGO_GEMM_REG) return StepsRoute::Loop;
+  return cheapest_steps(g, count, mode, clip_gemm_supported(g, T, y_cap_frames),
+                        gemm_steps_supported(g, T, y_cap_frames, x),
+                        reg_steps_supported(g, T, y_cap_frames));
 }
 
 co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* y,
                              int32_t y_cap_frames, int32_t pad_end, int32_t update_state,
-                             hipStream_t s, int32_t* n_out, const Scratch* sc) {
+                             hipStream_t s, int32_t* n_out, const Scratch* sc,
+                             StepsMode mode) {
   if (!live(h, HKind::Conv) || T < 0 || y_cap_frames < 0 || !n_out) return CO_EINVAL;
   if (T > 0 && !x) return CO_EINVAL;
   const ConvGeom& g = h->g;
@@ -198,7 +197,31 @@ co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* 
   if (n_emit > y_cap_frames) return CO_EINVAL;
   if (n_emit > 0 && !y) return CO_EINVAL;
   const int64_t n0 = h->n;
-  const StepsRoute route = count > 0 ? steps_route(g, T, y_cap_frames, x) : StepsRoute::Loop;
+  const int64_t S = g.S(), So = g.So();
+  const size_t esz = g.dtype == CO_BF16 ? 2 : 4;
+  const int64_t ring_bytes = int64_t(g.R) * h->L.ring_slot_elems * 4;
+  StepsRoute route =
+      count > 0 ? steps_route(g, T, count, y_cap_frames, x, mode) : StepsRoute::Loop;
+  // With a caller workspace, a loop takes from it the ring's backup first, then
+  // the staged copies of a frame the step kernel cannot read in place.  Whether
+  // a frame is staged depends on its pointer's alignment, which repeats every
+  // two frames, and on the plane strides, which every frame shares.  A call that
+  // needs more than there is goes to a launch that needs none, if one takes it.
+  const int64_t backup = update_state ? 0 : round256(ring_bytes);
+  if (route == StepsRoute::Loop && sc) {
+    int64_t stage = 0;
+    for (int64_t t = 0; t < std::min<int64_t>(T, 2); ++t) {
+      const StepIO io{static_cast<const char*>(x) + size_t(t * S) * esz, int64_t(T) * S,
+                      n_emit > 0 ? y : nullptr, int64_t(y_cap_frames) * So};
+      stage = std::max(stage, conv_step_staging_bytes(g, io));
+    }
+    if (backup + stage > sc->bytes) {
+      if (count > 0 && clip_gemm_supported(g, T, y_cap_frames)) route = StepsRoute::Clip;
+      else if (count > 0 && gemm_steps_supported(g, T, y_cap_frames, x)) route = StepsRoute::Gemm;
+      else if (count > 0 && reg_steps_supported(g, T, y_cap_frames)) route = StepsRoute::Reg;
+      else return CO_ESCRATCH;
+    }
+  }
   if (route != StepsRoute::Loop) {
     // one launch: partial sums stay on chip across frames; with
     // update_state = 0 the state is simply not written back
@@ -237,23 +260,6 @@ co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* 
     if (update_state) h->n += count;
     *n_out = int32_t(n_emit);
     return CO_OK;
-  }
-  const int64_t S = g.S(), So = g.So();
-  const size_t esz = g.dtype == CO_BF16 ? 2 : 4;
-  const int64_t ring_bytes = int64_t(g.R) * h->L.ring_slot_elems * 4;
-  // With a caller workspace: the ring's backup first, then the staged copies
-  // of a frame the step kernel cannot read in place.  Whether a frame is
-  // staged depends on its pointer's alignment, which repeats every two
-  // frames, and on the plane strides, which every frame shares.
-  const int64_t backup = update_state ? 0 : round256(ring_bytes);
-  if (sc) {
-    int64_t stage = 0;
-    for (int64_t t = 0; t < std::min<int64_t>(T, 2); ++t) {
-      const StepIO io{static_cast<const char*>(x) + size_t(t * S) * esz, int64_t(T) * S,
-                      n_emit > 0 ? y : nullptr, int64_t(y_cap_frames) * So};
-      stage = std::max(stage, conv_step_staging_bytes(g, io));
-    }
-    if (backup + stage > sc->bytes) return CO_ESCRATCH;
   }
   Backup bk;
   if (!update_state) {
@@ -431,7 +437,7 @@ co_status co_conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, voi
                                 int32_t y_cap_frames, int32_t pad_end, int32_t update_state,
                                 void* stream, int32_t* n_out) {
   return conv_forward_steps(h, x, T, y, y_cap_frames, pad_end, update_state, as_stream(stream),
-                            n_out, nullptr);
+                            n_out, nullptr, update_state ? StepsMode::Update : StepsMode::Peek);
 }
 
 co_status co_conv_forward_steps_noalloc(co_conv_handle* h, const void* x, int32_t T, void* y,
@@ -443,7 +449,7 @@ co_status co_conv_forward_steps_noalloc(co_conv_handle* h, const void* x, int32_
   if (st != CO_OK) return st;
   const Scratch sc{static_cast<char*>(p), kScratchBytes};
   return conv_forward_steps(h, x, T, y, y_cap_frames, pad_end, update_state, as_stream(stream),
-                            n_out, &sc);
+                            n_out, &sc, update_state ? StepsMode::Update : StepsMode::Peek);
 }
 
 co_status co_conv_scratch_bytes(int64_t* bytes) {
@@ -459,7 +465,20 @@ co_status co_conv_steps_fused(const co_conv_handle* h, int32_t T, int32_t y_cap_
   // (the GEMM family also needs 4-byte aligned pixel pairs in x; an
   // allocation from the caching allocator always is)
   static const uint32_t aligned_probe = 0;
-  *fused = steps_route(g, T, y_cap_frames, &aligned_probe) != StepsRoute::Loop ? 1 : 0;
+  const StepsRoute r = steps_route(g, T, T, y_cap_frames, &aligned_probe, StepsMode::Update);
+  *fused = r != StepsRoute::Loop ? 1 : 0;
+  return CO_OK;
+}
+
+co_status co_conv_steps_route(const co_conv_desc* desc, int32_t T, int32_t y_cap_frames,
+                              int32_t update_state, int32_t* route) {
+  if (!route || T < 0 || y_cap_frames < 0) return CO_EINVAL;
+  ConvGeom g;
+  const co_status st = conv_geom(desc, &g);
+  if (st != CO_OK) return st;
+  static const uint32_t aligned_probe = 0;
+  *route = int32_t(steps_route(g, T, T, y_cap_frames, &aligned_probe,
+                               update_state ? StepsMode::Update : StepsMode::Peek));
   return CO_OK;
 }
 
@@ -504,9 +523,12 @@ co_status co_conv_forward_ws(const co_conv_desc* desc, const void* weight, const
   if (st != CO_OK) return st;
   // (a one-launch call need not leave a state behind; a loop keeps its
   // partial sums in it)
-  const int32_t update = steps_route(g, T, int32_t(T_out), x) == StepsRoute::Loop ? 1 : 0;
+  const StepsMode mode = StepsMode::Clip;
+  const int32_t update =
+      steps_route(g, T, int64_t(T) + g.pT, int32_t(T_out), x, mode) == StepsRoute::Loop ? 1 : 0;
   int32_t n = 0;
-  st = conv_forward_steps(h, x, T, y, int32_t(T_out), 1, update, as_stream(stream), &n, nullptr);
+  st = conv_forward_steps(h, x, T, y, int32_t(T_out), 1, update, as_stream(stream), &n, nullptr,
+                          mode);
   co_conv_destroy(h);
   if (st == CO_OK && n != T_out) return CO_EINVAL;  // (Principle 4: cannot happen)
   return st;

@@ -94,7 +94,7 @@ struct ClipArgs {
   int32_t act;
   int32_t unpadded;  // one spatial tap, no padding: every pixel's lies in its plane
   int32_t win_rows;  // WINDOW: staged pixels, a multiple of 128
-  FastDiv fd_nrb, fd_B, fd_nt, fd_So, fd_Wo, fd_R, fd_nq, fd_q, fd_kW, fd_wcols, fd_dT;
+  FastDiv fd_nrb, fd_B, fd_nt, fd_So, fd_Wo, fd_R, fd_q, fd_kW, fd_wcols, fd_dT;
 };
 
 template <typename T>
@@ -716,45 +716,6 @@ hipError_t clip_launch(ClipCall& c) {
   return hipGetLastError();
 }
 
-// bf16 layers with one spatial tap and stride 1 gather pixel pairs (from
-// planes of two pixels at least).
-bool clip_pairs(const ConvGeom& g) {
-  return g.dtype == CO_BF16 && g.kH * g.kW == 1 && g.sT == 1 && g.sH == 1 && g.sW == 1 &&
-         g.pH == 0 && g.pW == 0;
-}
-
-// Layers whose one spatial tap never leaves the plane (no bound on its sides).
-bool clip_unpadded(const ConvGeom& g) { return g.kH * g.kW == 1 && g.pH == 0 && g.pW == 0; }
-
-// Workgroups of `tile` channels that `outputs` output frames take.
-int64_t clip_wgs(const ConvGeom& g, int64_t outputs, int tile) {
-  return ceil_div(outputs * g.So(), 128) * g.B * ceil_div(g.Cout, tile);
-}
-
-// Channel tile: the least padded width times (1 + what a tile's input staging
-// costs against its matrix work, about 32 channels' worth).  Where bf16
-// gathers pixel by pixel and there is work for two workgroups a CU, 192
-// channels take the taller wave tile (128 x 48): the waves of a workgroup then
-// share no weights, and a weight fragment fetched through L1 feeds eight
-// instructions instead of four (64 streams, 192 -> 192, 3x3x3, 14x14, 16
-// frames: 667 us against 1010 us in 96-channel tiles; 16 streams, 8 frames:
-// 229 against 219).
-int clip_tile(const ConvGeom& g, int64_t outputs) {
-  int best = 0;
-  int64_t cost = 0;
-  for (const int n : {32, 64, 96, 128}) {
-    const int64_t c = ceil_div(g.Cout, n) * (n + 32);
-    if (best == 0 || c < cost) {
-      best = n;
-      cost = c;
-    }
-  }
-  if (best == 96 && g.dtype == CO_BF16 && !clip_pairs(g) && clip_wgs(g, outputs, 192) >= 512 &&
-      ceil_div(g.Cout, 192) * 192 <= ceil_div(g.Cout, 96) * 96)
-    return 192;
-  return best;
-}
-
 template <typename T, bool PAIR, bool WINDOW>
 hipError_t clip_dispatch(ClipCall& c, int tile) {
   switch (tile) {
@@ -765,33 +726,6 @@ hipError_t clip_dispatch(ClipCall& c, int tile) {
   }
   if constexpr (sizeof(T) == 2 && !PAIR) return clip_launch<T, 8, 3, 1, 4, PAIR, WINDOW>(c);
   return hipErrorInvalidValue;
-}
-
-// Measured time of a clip GEMM call in microseconds.  A workgroup's k-step
-// takes `latency` while the CUs have one workgroup each, and beyond that
-// `rate` for every workgroup on the fullest CU, in proportion to its channels
-// (bf16 tiles narrower than 96 channels cost as much); the second pass's
-// workgroups walk about half their taps again.
-double clip_us(const ConvGeom& g, int64_t frames) {
-  const bool bf = g.dtype == CO_BF16;
-  const int tile = clip_tile(g, ceil_div(frames, g.sT));
-  const double latency = !bf ? 1.15 : clip_pairs(g) ? 0.55 : 0.85;
-  const double rate = bf ? 0.5 : 1.1;
-  const double ksteps = double(g.kT) * g.kH * g.kW * ceil_div(g.Cin, bf ? 32 : 16);
-  const double wide = double(bf ? std::max(tile, 96) : tile) / 128;
-  auto passes = [&](int64_t outputs) {
-    return ksteps *
-           std::max(latency, rate * wide * double(ceil_div(clip_wgs(g, outputs, tile), 256)));
-  };
-  return 8 + passes(ceil_div(frames, g.sT)) + (g.R > 1 ? 0.5 * passes(g.R) : 0);
-}
-
-// The same of a call that runs step by step: a launch and the step kernels'
-// measured rates.
-double loop_us(const ConvGeom& g, int64_t frames) {
-  const double mflops = 2e-6 * g.B * g.So() * g.Cout * g.kT * g.Cin * g.kH * g.kW / g.sT;
-  const double tflops = g.algo == CO_ALGO_GEMM_REG ? 70 : g.dtype == CO_BF16 ? 1000 : 75;
-  return double(frames) * ((g.algo == CO_ALGO_GEMM_REG ? 5 : 8) + mflops / tflops);
 }
 
 }  // namespace
@@ -815,41 +749,6 @@ bool clip_gemm_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames) 
          int64_t(g.B) * g.Cout * y_frames * g.So() * esz < lim &&
          (x_frames + g.f) * g.So() < lim / 4 && int64_t(g.R) * L.ring_slot_elems * 4 < lim &&
          L.weight_bytes < lim;
-}
-
-bool clip_gemm_preferred(const ConvGeom& g, int64_t x_frames, bool gemm_steps, bool reg_steps) {
-  // one temporal tap: the frames are independent, a plain GEMM over all of
-  // them (4.9x to 2.5x the persistent kernels', 1.3x and more that of two
-  // steps)
-  if (g.kT == 1 && (x_frames >= 2 || reg_steps)) return true;
-  GemmStepsConfig sc;
-  RegConfig c;
-  if (gemm_steps_config(g, &sc)) {
-    if (g.kH * g.kW == 1) return true;
-    if (gemm_steps) {
-      // the persistent 3x3 GEMM walks the frames, about 3.3 us a frame and 32
-      // channels for every 256 workgroups (160 pixels x 64 channels): it keeps
-      // the layers that fill the chip with them
-      const double rounds = double(ceil_div(int64_t(sc.m_tiles) * sc.o_tiles, 256));
-      return clip_us(g, x_frames) < 8 + x_frames * rounds * sc.n_chunks * 3.3;
-    }
-  } else if (reg_config(g, g.cfg, &c) && g.algo == CO_ALGO_GEMM_REG) {
-    if (c.TAPS > 1) {
-      // 3x3 shapes keep their partial sums and weights in registers
-      if (reg_steps) return false;
-    } else if (c.id != 7 && g.kT <= (c.id == 1 ? 3 : 9)) {
-      // Persistent kernels at their own kT.  bf16 with at most 64 channels:
-      // their eight-wave workgroups win where about a hundred of them share
-      // the frames (32 streams, 64 -> 256, kT 9, 25 joints, 300 frames: 102 us
-      // against 130; 16 streams: 116 us against 81).  fp32: at kT 3 up to 256
-      // tiles (28 us against 35).  Everything else goes this way: any kT,
-      // stride and dilation (2x to 11x what persistent forms of those took).
-      const int64_t tiles = int64_t(c.m_frags) * ceil_div(g.Cout, 16);
-      if (!reg_steps) return true;
-      return g.dtype == CO_BF16 ? tiles < 8 * 90 : tiles > 256;
-    }
-  }
-  return clip_us(g, x_frames) < loop_us(g, x_frames);
 }
 
 hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* state,
@@ -918,7 +817,6 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   ca.fd_Wo = make_fastdiv(uint32_t(g.Wo));
   ca.fd_R = make_fastdiv(uint32_t(g.R));
   ca.fd_dT = make_fastdiv(uint32_t(g.dT));
-  ca.fd_nq = make_fastdiv(uint32_t(ca.nq));
   ca.fd_q = make_fastdiv(uint32_t(ca.tap_outer ? CS : ntaps));
   ca.fd_kW = make_fastdiv(uint32_t(g.kW));
   ca.fd_wcols = make_fastdiv(uint32_t(ca.wcols));

@@ -134,9 +134,8 @@ hipError_t launch_conv_step_gemm(const ConvGeom& g, const ConvLayout& L, char* s
 hipError_t launch_conv_step_reg(const ConvGeom& g, const ConvLayout& L, char* state,
                                 const StepIO& io, const co_step_plan& plan, hipStream_t stream);
 // Persistent forward_steps of the register-GEMM step (same conventions as
-// the depthwise one): temporal stride and dilation 1, kT within what the
-// step kernel's instantiation can hold in registers (3x3 taps), or a kT at
-// which it beats the GEMM over all frames (one tap).
+// the depthwise one): temporal stride 1 and dilation 1, kT within what the
+// step kernel's instantiation can hold in registers.
 bool reg_steps_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames);
 hipError_t launch_conv_steps_reg(const ConvGeom& g, const ConvLayout& L, char* state,
                                  const void* x, int64_t x_bc, int32_t T, int32_t count, void* y,
@@ -156,10 +155,24 @@ hipError_t launch_conv_steps_gemm(const ConvGeom& g, const ConvLayout& L, char* 
 // dilation; same bits as stepping.  act applies to the emitted, rounded
 // frames as launch_act would.
 bool clip_gemm_supported(const ConvGeom& g, int64_t x_frames, int64_t y_frames);
-// Whether it is the faster way for a supported call, against the persistent
-// GEMM or register-GEMM kernel where one of them takes the call, else
-// against single steps.
-bool clip_gemm_preferred(const ConvGeom& g, int64_t x_frames, bool gemm_steps, bool reg_steps);
+// Its layers of one spatial tap that never leaves the plane (no bound on its
+// sides), those that gather pixel pairs (from planes of two pixels at least),
+// and its channel tile for a number of output frames.
+bool clip_unpadded(const ConvGeom& g);
+bool clip_pairs(const ConvGeom& g);
+int clip_tile(const ConvGeom& g, int64_t outputs);
+
+// How a forward_steps call runs: as a loop of steps, or as one launch of a
+// family's kernel or of the GEMM over frames (the values are CO_STEPS_*).
+enum class StepsRoute : int32_t { Loop, Depthwise, DirectMma, Direct, Gemm, Reg, Clip };
+// Whether the call updates the state, leaves it alone, or runs a whole clip
+// over a state of its own, which nobody reads afterwards.
+enum class StepsMode { Update, Peek, Clip };
+// The fastest of the ways that take a matrix-core layer's call over this many
+// frames (steps_cost.cpp): the GEMM over frames, the persistent GEMM and
+// register GEMM where they take it, and the loop.
+StepsRoute cheapest_steps(const ConvGeom& g, int64_t frames, StepsMode mode, bool clip, bool gemm,
+                          bool reg);
 hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* state,
                                  const void* x, int64_t x_bc, int32_t T, int32_t count, void* y,
                                  int64_t y_bc, int64_t n0, bool update, int32_t act,
