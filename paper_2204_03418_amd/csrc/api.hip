@@ -1208,7 +1208,14 @@ co_status co_bneck_forward_step(co_bneck_handle* h, const void* x_t, void* z_t,
 co_status co_bneck_workspace_bytes(const co_bneck_handle* h, int32_t T, int64_t* bytes) {
   if (!live_bneck(h) || T < 0 || !bytes) return CO_EINVAL;
   const int64_t frame = bneck_frame_bytes(h);
-  const int64_t chunk = bneck_chunk(h, T, std::max(kBneckWsBytes, kBneckWsFrames * frame));
+  int64_t chunk = bneck_chunk(h, T, std::max(kBneckWsBytes, kBneckWsFrames * frame));
+  // Two frames of a small layer: two fused launches take 17 us of mostly host
+  // time, the other two and the workspace 18 to 20 (96 -> 216, 5x5, float32).
+  // Larger pointwise layers make a fused step long (192 -> 432, 7x7, float32 66
+  // against 42, bf16 of 16 streams 23 against 18, of one 18 against 19).
+  const ConvGeom& g = h->pw->g;
+  const int64_t macs = int64_t(g.B) * g.So() * g.Cin * g.Cout;
+  if (T == 2 && !(g.dtype == CO_F32 && g.Cin >= 128) && macs < 30000000) chunk = 0;
   *bytes = chunk < 2 ? 0 : chunk * frame;
   return CO_OK;
 }

@@ -59,6 +59,23 @@ def test_bottleneck_chunks(case, frames):
         assert torch.equal(outs[i], w) and torch.equal(peek[:, :, i], w)
 
 
+@pytest.mark.parametrize("case", BNECK_CASES, ids=lambda c: f"bneck_{c[6]}_{c[-1]}_{c[1]}")
+def test_bottleneck_workspace_bytes(case):
+    """The chunk tests above have layers that the two launches take, and the
+    library asks for a workspace from three frames on (of a small layer)."""
+    _, modules, _, _ = _bneck_parts(case, 5690)
+    pw, dw, pool = modules()
+    bn = coinf.Bottleneck(pw, case[8], dw, case[9], pool)
+    nb = coinf.i64()
+
+    def frames(T):
+        assert coinf.co_bneck_workspace_bytes(bn.handle, T, ctypes.byref(nb)) == coinf.CO_OK
+        return nb.value // (pw.batch * pw.out_channels * pw.in_size[0] * pw.in_size[1] *
+                            (2 if case[-1] == "bf16" else 4))
+
+    assert [frames(T) for T in (0, 1, 2, 3, 16)] == [0, 0, 0, 3, 16]
+
+
 def test_bottleneck_workspace_past_the_launches():
     """A workspace that holds more frames than one launch addresses (2 GiB of
     pointwise frames) is used in chunks that a launch takes."""
