@@ -68,14 +68,7 @@ constexpr int kNoFrame = -(1 << 29);
 
 enum ClipPack : int32_t { kPackReg = 0, kPackGemm = 1, kPackWs = 2 };
 
-struct ClipArgs {
-  int32_t E, nu;     // outputs the call completes; outputs it touches
-  int32_t c0;        // call frame of tap 0 of output 0 (the first completed one)
-  int32_t n0;        // frames before the call (capped: only t >= -n0 matters)
-  int32_t T, S, So;  // real frames; pixels per input and output frame
-  int32_t slot0;     // ring slot of output 0
-  int32_t R;
-  int32_t tail;      // unfinished outputs go to the ring
+struct ClipArgs : FrameSpan {
   int32_t shift;     // pixels by which the tiles begin early (see PAIR)
   int32_t m_pairs, n_tiles;  // (pixel tile, stream) pairs; channel tiles
   int32_t y_bytes, w_bytes, ring_bytes;
@@ -201,17 +194,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
 
   // the outputs of the unfinished pass: pixel m of the first R outputs'
   // stands for that pixel of the unfinished output in the same slot
-  auto tail_output = [&](int tau) {
-    const int k = ca.E > tau ? fdiv(ca.E - tau + ca.R - 1, ca.fd_R) : 0;
-    return tau + k * ca.R;
-  };
-  // whether output tau continues a partial sum: one of its taps fell on a
-  // frame of the stream before the call (no branches: the loads it guards
-  // issue together)
-  auto continues = [&](int t0) {
-    const int j = fdiv(max(0, -ca.n0 - t0 + g.dT - 1), ca.fd_dT);  // first tap in the stream
-    return (t0 < 0) & (j < g.kT) & (t0 + j * g.dT < 0);
-  };
+  auto open_output = [&](int tau) { return tail_output(ca.E, ca.R, ca.fd_R, tau); };
+  auto continues = [&](int t0) { return continues_sum(ca.n0, g.kT, g.dT, ca.fd_dT, t0); };
 
   // a copy the compiler cannot trace: the pixel arithmetic of the prologue and
   // the epilogue is the same in both passes, and kept in registers across the
@@ -296,7 +280,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
         int to = tau;
         bool in = m >= 0;
         if (pass == 1) {  // uniform
-          to = tail_output(tau);
+          to = open_output(tau);
           in = in & (tau < ca.R) & (to < ca.nu);
         }
         const int t0 = to * g.sT + ca.c0;
@@ -324,7 +308,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
         for (int r = 0; r < 4; ++r) {
           const int m = m0h + wm * (16 * WMF) + mf * 16 + lgrp * 4 + r;
           const int tau = fdiv(max(m, 0), ca.fd_So), p = m - tau * ca.So;
-          const int to = pass == 0 ? tau : tail_output(tau);
+          const int to = pass == 0 ? tau : open_output(tau);
           const bool in = (m >= 0) & (pass == 0 ? to < ca.E : (tau < ca.R) & (to < ca.nu)) &
                           continues(to * g.sT + ca.c0);
           const int s = ca.slot0 + to;
@@ -663,7 +647,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, WMF * WNF > (WINDOW ? 8 : 16) ? 2 :
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int tau = fdiv(max(m + r, 0), ca.fd_So), p = m + r - tau * ca.So;
-          const int to = tail_output(tau);
+          const int to = open_output(tau);
           const bool in = (m + r >= 0) & (tau < ca.R) & (to < ca.nu);
           const int s = ca.slot0 + to;
           const int off = (s - fdiv(s, ca.fd_R) * ca.R) * ca.ring_slot + b * ca.So + p;
@@ -758,22 +742,7 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
   ClipCall c{&g, &L, state, x, y, ClipArgs{}, s};
   ClipArgs& ca = c.ca;
-  // outputs by the frames their taps reach: output tau completes at virtual
-  // time tau sT + (kT - 1) dT, the call spans [v0, v0 + count)
-  const int64_t v0 = n0 + g.pT;
-  const int64_t span = int64_t(g.kT - 1) * g.dT;
-  const int64_t tau0 = v0 > span ? ceil_div(v0 - span, g.sT) : 0;
-  ca.E = int32_t(conv_emissions(g, n0, count));
-  const int64_t tau1 = ceil_div(v0 + count, g.sT);  // first output past the call
-  ca.nu = int32_t(std::max<int64_t>(tau1 - tau0, ca.E));
-  ca.c0 = int32_t(tau0 * g.sT - v0);
-  ca.n0 = int32_t(std::min<int64_t>(n0, int64_t(1) << 28));
-  ca.T = nreal;
-  ca.S = int32_t(g.S());
-  ca.So = int32_t(g.So());
-  ca.slot0 = int32_t(tau0 % g.R);
-  ca.R = g.R;
-  ca.tail = update && ca.nu > ca.E ? 1 : 0;
+  static_cast<FrameSpan&>(ca) = frame_span(g, n0, nreal, count, update);
   ca.plane = int32_t(x_bc);
   ca.span = int32_t(int64_t(nreal) * g.S());
   ca.y_bc = int32_t(y_bc);
@@ -832,7 +801,7 @@ hipError_t launch_conv_clip_gemm(const ConvGeom& g, const ConvLayout& L, char* s
   // slots wrap around to output E at the pixel (E mod R) So of a tile row
   ca.shift = ca.tail ? int32_t((int64_t(ca.E % g.R) * ca.So) & 1) : 0;
   // the tile's pixels and those its later taps add, in LDS at once
-  const int64_t rows = round_up(128 + span * ca.S, 128);
+  const int64_t rows = round_up(128 + int64_t(g.kT - 1) * g.dT * ca.S, 128);
   if (g.kT > 1 && rows * ca.nq * 64 <= kClipWindowBytes) {
     ca.win_rows = int32_t(rows);
     ca.fd_nrb = make_fastdiv(uint32_t(rows / 128));

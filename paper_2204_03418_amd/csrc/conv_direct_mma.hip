@@ -49,13 +49,7 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // A call frame that no tap moves into the call.
 constexpr int kNoFrame = -(1 << 29);
 
-struct DmArgs {
-  int32_t E, nu;     // outputs the call completes; outputs it touches
-  int32_t c0;        // call frame of tap 0 of output 0 (the first completed one)
-  int32_t n0;        // frames before the call (capped: only t >= -n0 matters)
-  int32_t T, S, So;  // real frames; pixels per input and output frame
-  int32_t slot0, R;  // ring slot of output 0; ring slots
-  int32_t tail;      // unfinished outputs go to the ring
+struct DmArgs : FrameSpan {
   int32_t m_pairs, n_tiles;  // (pixel tile, stream) pairs; channel tiles
   int32_t plane, x_bytes;    // elements between input channels; a stream's bytes
   int32_t y_bc, y_bytes;     // elements between output channels; a stream's bytes
@@ -113,16 +107,8 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
   auto oc = [&](int f) { return nt * N_WG + (wn * WNF + f) * 16 + lrow; };
   // the outputs of the unfinished pass: pixel m of the first R outputs'
   // stands for that pixel of the unfinished output in the same slot
-  auto tail_output = [&](int tau) {
-    const int k = ca.E > tau ? fdiv(ca.E - tau + ca.R - 1, ca.fd_R) : 0;
-    return tau + k * ca.R;
-  };
-  // whether an output with tap 0 at call frame t0 continues a partial sum:
-  // one of its taps fell on a frame of the stream before the call
-  auto continues = [&](int t0) {
-    const int j = fdiv(max(0, -ca.n0 - t0 + g.dT - 1), ca.fd_dT);  // first tap in the stream
-    return (t0 < 0) & (j < g.kT) & (t0 + j * g.dT < 0);
-  };
+  auto open_output = [&](int tau) { return tail_output(ca.E, ca.R, ca.fd_R, tau); };
+  auto continues = [&](int t0) { return continues_sum(ca.n0, g.kT, g.dT, ca.fd_dT, t0); };
   // a copy the compiler cannot trace: the pixel arithmetic of the prologue and
   // the epilogue is the same in both passes, and kept in registers across the
   // K loop it would spill
@@ -143,7 +129,7 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
       if (last - first < 4) {
         int lo = ca.nu, hi = -1;
         for (int tau = first; tau <= last; ++tau) {
-          const int to = tail_output(tau);
+          const int to = open_output(tau);
           if (to < ca.nu) {
             lo = min(lo, to);
             hi = max(hi, to);
@@ -171,7 +157,7 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
     for (int i = 0; i < MB; ++i) {
       const int m = m0 + i * 64 + lane;
       const int tau = fdiv(m, ca.fd_So), p = m - tau * ca.So;
-      const int to = pass == 0 ? tau : tail_output(tau);
+      const int to = pass == 0 ? tau : open_output(tau);
       const bool in = pass == 0 ? tau < ca.E : (tau < ca.R) & (to < ca.nu);
       const int t0 = to * g.sT + ca.c0 + j_lo * g.dT;
       fr[i] = in ? t0 : kNoFrame;
@@ -203,7 +189,7 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
         for (int r = 0; r < 4; ++r) {
           const int m = m0h + wm * (16 * WMF) + mf * 16 + lgrp * 4 + r;
           const int tau = fdiv(m, ca.fd_So), p = m - tau * ca.So;
-          const int to = pass == 0 ? tau : tail_output(tau);
+          const int to = pass == 0 ? tau : open_output(tau);
           const bool in = (pass == 0 ? to < ca.E : (tau < ca.R) & (to < ca.nu)) &
                           continues(to * g.sT + ca.c0);
           const int s = ca.slot0 + to;
@@ -414,7 +400,7 @@ __global__ __launch_bounds__(256, MB * WNF > 6 ? 2 : 3) void conv_direct_mma_ker
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int tau = fdiv(m + r, ca.fd_So), p = m + r - tau * ca.So;
-          const int to = tail_output(tau);
+          const int to = open_output(tau);
           const bool in = (tau < ca.R) & (to < ca.nu);
           const int s = ca.slot0 + to;
           const int off = (s - fdiv(s, ca.fd_R) * ca.R) * ca.ring_slot + b * ca.So + p;
@@ -527,22 +513,7 @@ hipError_t launch_direct_mma(const ConvGeom& g, const ConvLayout& L, char* state
   const int64_t esz = g.dtype == CO_BF16 ? 2 : 4;
   DmCall c{&g, &L, state, x, int64_t(g.Cin) * x_bc, y, int64_t(g.Cout) * y_bc, DmArgs{}, s};
   DmArgs& ca = c.ca;
-  // outputs by the frames their taps reach: output tau completes at virtual
-  // time tau sT + (kT - 1) dT, the call spans [v0, v0 + count)
-  const int64_t v0 = n0 + g.pT;
-  const int64_t span = int64_t(g.kT - 1) * g.dT;
-  const int64_t tau0 = v0 > span ? ceil_div(v0 - span, g.sT) : 0;
-  ca.E = int32_t(conv_emissions(g, n0, count));
-  const int64_t tau1 = ceil_div(v0 + count, g.sT);  // first output past the call
-  ca.nu = int32_t(std::max<int64_t>(tau1 - tau0, ca.E));
-  ca.c0 = int32_t(tau0 * g.sT - v0);
-  ca.n0 = int32_t(std::min<int64_t>(n0, int64_t(1) << 28));
-  ca.T = nreal;
-  ca.S = int32_t(g.S());
-  ca.So = int32_t(g.So());
-  ca.slot0 = int32_t(tau0 % g.R);
-  ca.R = g.R;
-  ca.tail = update && ca.nu > ca.E ? 1 : 0;
+  static_cast<FrameSpan&>(ca) = frame_span(g, n0, nreal, count, update);
   ca.plane = int32_t(x_bc);
   ca.x_bytes = int32_t((int64_t(g.Cin - 1) * x_bc + int64_t(nreal) * g.S()) * esz);
   ca.y_bc = int32_t(y_bc);

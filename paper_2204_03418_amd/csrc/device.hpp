@@ -60,6 +60,21 @@ struct PoolTaps {
   int32_t src[CO_MAX_TAPS];
 };
 
+// Outputs of a GEMM over frames (FrameSpan).  The unfinished output in the ring
+// slot of output tau (tau < R), fd_R dividing by R.
+__device__ __forceinline__ int tail_output(int E, int R, const FastDiv& fd_R, int tau) {
+  const int k = E > tau ? fdiv(E - tau + R - 1, fd_R) : 0;
+  return tau + k * R;
+}
+// Whether an output with tap 0 at call frame t0 continues a partial sum: one of
+// its taps fell on one of the stream's n0 frames before the call (no branches:
+// the loads it guards issue together; fd_dT divides by dT).
+__device__ __forceinline__ bool continues_sum(int n0, int kT, int dT, const FastDiv& fd_dT,
+                                              int t0) {
+  const int j = fdiv(max(0, -n0 - t0 + dT - 1), fd_dT);  // first tap in the stream
+  return (t0 < 0) & (j < kT) & (t0 + j * dT < 0);
+}
+
 constexpr int kBlock = 256;
 
 // Raw buffer resource over `bytes` bytes from `base` (CDNA raw-buffer word 3:

@@ -530,6 +530,27 @@ int64_t conv_emissions(const ConvGeom& g, int64_t n, int64_t count) {
   return (hi - 1 - first) / g.sT + 1;
 }
 
+FrameSpan frame_span(const ConvGeom& g, int64_t n0, int32_t nreal, int32_t count, bool update) {
+  FrameSpan f;
+  // output tau completes at virtual time tau sT + (kT - 1) dT, the call spans
+  // [v0, v0 + count)
+  const int64_t v0 = n0 + g.pT;
+  const int64_t span = int64_t(g.kT - 1) * g.dT;
+  const int64_t tau0 = v0 > span ? ceil_div(v0 - span, g.sT) : 0;
+  const int64_t tau1 = ceil_div(v0 + count, g.sT);  // first output past the call
+  f.E = int32_t(conv_emissions(g, n0, count));
+  f.nu = int32_t(std::max<int64_t>(tau1 - tau0, f.E));
+  f.c0 = int32_t(tau0 * g.sT - v0);
+  f.n0 = int32_t(std::min<int64_t>(n0, int64_t(1) << 28));
+  f.T = nreal;
+  f.S = int32_t(g.S());
+  f.So = int32_t(g.So());
+  f.slot0 = int32_t(tau0 % g.R);
+  f.R = g.R;
+  f.tail = update && f.nu > f.E ? 1 : 0;
+  return f;
+}
+
 co_status pool_geom(const co_pool_desc* desc, PoolGeom* g) {
   if (!desc || !g) return CO_EINVAL;
   const co_pool_desc& d = *desc;

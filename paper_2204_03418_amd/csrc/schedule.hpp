@@ -240,6 +240,20 @@ void plan_table(const ConvGeom& g, int64_t n0, int64_t count, PlanTable* t);
 // Number of non-empty outputs of steps n .. n + count - 1.
 int64_t conv_emissions(const ConvGeom& g, int64_t n, int64_t count);
 
+// A call of the GEMMs over frames (conv_clip.hip, conv_direct_mma.hip) by its
+// outputs: those it completes, counted from the first, then those that its
+// frames touch and that stay unfinished.
+struct FrameSpan {
+  int32_t E, nu;     // outputs the call completes; outputs it touches
+  int32_t c0;        // call frame of tap 0 of output 0 (the first completed one)
+  int32_t n0;        // frames before the call (capped: only t >= -n0 matters)
+  int32_t T, S, So;  // real frames; pixels per input and output frame
+  int32_t slot0;     // ring slot of output 0
+  int32_t R;         // ring slots
+  int32_t tail;      // unfinished outputs go to the ring
+};
+FrameSpan frame_span(const ConvGeom& g, int64_t n0, int32_t nreal, int32_t count, bool update);
+
 co_status pool_geom(const co_pool_desc* desc, PoolGeom* g);
 PoolLayout pool_layout(const PoolGeom& g);
 uint64_t pool_hash(const PoolGeom& g);
