@@ -14,8 +14,11 @@
 // times measured on MI355X: 1924 calls of 29 layers (skeleton, pointwise and
 // video layers, 24 to 432 channels, kT 1 to 9, temporal stride 1 and 2, both
 // dtypes) with 1 to 64 streams and 2 to 300 frames, whose frames change from
-// call to call.  Taking the cheapest by these estimates costs 0.6% over the best
-// way on average, less than 2% in 95 of 100 calls and 1.7x in the worst.
+// call to call.  A clip of 300 frames beyond about 100 MB counts with the mean
+// of changing and of repeated frames: the bf16 persistent kernels gain a third
+// from frames that the memory-side cache holds, the GEMM a tenth.  Taking the
+// cheapest by these estimates costs 0.6% over the best way on average, less than
+// 2% in 95 of 100 calls and 1.5x in the worst.
 #include <algorithm>
 
 #include "launch.hpp"
@@ -103,7 +106,7 @@ double loop_us(const ConvGeom& g, int64_t frames) {
   const double mflops = 2e-6 * g.B * g.So() * g.Cout * g.kT * g.Cin * g.kH * g.kW / g.sT;
   double us;
   if (g.algo == CO_ALGO_GEMM_REG) {
-    us = 4.6 + mflops / 100;
+    us = 4.6 + mflops / (g.dtype == CO_BF16 ? 100 : 75);
   } else {
     GemmConfig c;
     if (!gemm_config(g, g.cfg, &c)) return 0;
@@ -148,16 +151,16 @@ double reg_steps_us(const ConvGeom& g, const RegConfig& c, int64_t frames) {
   const double waves = double(wgs * sw * segs);
   if (!plain) {
     const double frame = bf ? 0.054 * work : 0.98 + 0.005 * work;
-    const double share = 1 + (bf ? 0.143 : 0.862) * std::max(0.0, waves / 1024 - 1);
-    return std::max(kCallUs, 7.6 + walk * frame * share + (bf ? 0.164 : 0.0) * mb);
+    const double share = 1 + (bf ? 0.146 : 0.863) * std::max(0.0, waves / 1024 - 1);
+    return std::max(kCallUs, 7.6 + walk * frame * share + (bf ? 0.159 : 0.0) * mb);
   }
   struct Fit {
     double start, once, load, frame, per, mb;
   };
-  const Fit f = c.id == 0   ? Fit{8.21, 0, 0.125, 0.995, 0.006, 0.309}
-                : c.id == 1 ? Fit{8.06, 0.025, 0.025, 0.111, 0.014, 0.166}
-                : c.id == 5 ? Fit{8.04, 0.198, 0.198, 0.555, 0, 0.205}
-                            : Fit{3.02, 0.168, 0.201, 0.385, 0.004, 0.165};
+  const Fit f = c.id == 0   ? Fit{8.00, 0, 0.131, 0.300, 0.011, 0.300}
+                : c.id == 1 ? Fit{8.30, 0.039, 0.039, 1.451, 0, 0.196}
+                : c.id == 5 ? Fit{8.00, 0.168, 0.168, 0.300, 0, 0.347}
+                            : Fit{8.05, 0.131, 0.131, 0.651, 0, 0};
   const double rounds = double(ceil_div(wgs * sw * segs, 1024 * wpe));
   return std::max(kCallUs, f.start + f.once * work +
                                rounds * (f.load * work + walk * (f.frame + f.per * work)) +

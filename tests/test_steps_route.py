@@ -38,7 +38,10 @@ MEASURED = [
     ("bf16", 64, 128, 128, dict(kernel=(3, 1), in_size=(25,)), 8, ("reg",)),          # 25/12/46
     ("bf16", 32, 128, 128, SKELETON, 8, ("reg",)),                                    # 51/19/51
     ("bf16", 16, 64, 256, SKELETON, 8, ("reg",)),                                     # 38/19/49
-    ("bf16", 32, 64, 256, SKELETON, 300, ("clip",)),                                  # 142/149/-
+    ("bf16", 32, 64, 256, SKELETON, 300, ("reg",)),  # 142/149/- (129/97 with repeated frames)
+    ("bf16", 16, 64, 256, SKELETON, 300, ("clip",)),                                  # 67/111/-
+    ("bf16", 64, 64, 64, SKELETON, 300, ("clip",)),                                   # 81/111/-
+    ("f32", 64, 64, 256, SKELETON, 8, ("reg",)),                                      # 93/64/105
     ("bf16", 64, 128, 128, dict(kernel=(3, 1), in_size=(25,)), 300, ("clip",)),       # 104/253/-
     ("f32", 1, 128, 128, dict(kernel=(3, 1), in_size=(25,), stride=(2, 1)), 8, ("reg",)),  # 57/16/40
     ("f32", 1, 128, 128, dict(kernel=(3, 1), in_size=(25,), stride=(2, 1)), 300, ("reg",)),  # 57/35/-
