@@ -159,6 +159,12 @@ co_status scratch_address(hipStream_t stream, void** out) {
   return CO_OK;
 }
 
+// Whether stream s records a graph (the null stream cannot).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 int64_t round256(int64_t n) { return (n + 255) & ~int64_t(255); }
 
 // Caller-side device workspace of a forward_steps call (null: the call makes
@@ -206,20 +212,21 @@ co_status conv_forward_steps(co_conv_handle* h, const void* x, int32_t T, void* 
   // the staged copies of a frame the step kernel cannot read in place.  Whether
   // a frame is staged depends on its pointer's alignment, which repeats every
   // two frames, and on the plane strides, which every frame shares.  A call that
-  // needs more than there is goes to a launch that needs none, if one takes it.
+  // needs more than there is goes to a launch that needs none, if one takes it,
+  // and so does one that would have to allocate it while the stream is captured.
   const int64_t backup = update_state ? 0 : round256(ring_bytes);
-  if (route == StepsRoute::Loop && sc) {
+  if (route == StepsRoute::Loop && count > 0 && (sc || capturing(s))) {
     int64_t stage = 0;
     for (int64_t t = 0; t < std::min<int64_t>(T, 2); ++t) {
       const StepIO io{static_cast<const char*>(x) + size_t(t * S) * esz, int64_t(T) * S,
                       n_emit > 0 ? y : nullptr, int64_t(y_cap_frames) * So};
       stage = std::max(stage, conv_step_staging_bytes(g, io));
     }
-    if (backup + stage > sc->bytes) {
-      if (count > 0 && clip_gemm_supported(g, T, y_cap_frames)) route = StepsRoute::Clip;
-      else if (count > 0 && gemm_steps_supported(g, T, y_cap_frames, x)) route = StepsRoute::Gemm;
-      else if (count > 0 && reg_steps_supported(g, T, y_cap_frames)) route = StepsRoute::Reg;
-      else return CO_ESCRATCH;
+    if (backup + stage > (sc ? sc->bytes : 0)) {
+      if (clip_gemm_supported(g, T, y_cap_frames)) route = StepsRoute::Clip;
+      else if (gemm_steps_supported(g, T, y_cap_frames, x)) route = StepsRoute::Gemm;
+      else if (reg_steps_supported(g, T, y_cap_frames)) route = StepsRoute::Reg;
+      else if (sc) return CO_ESCRATCH;
     }
   }
   if (route != StepsRoute::Loop) {

@@ -75,3 +75,36 @@ def test_persistent_route(case):
     assert d.steps == 3 and torch.equal(d.state, before)
     assert same(d.forward_steps(part), frames(3, T + 3))
     assert all(same(d.forward_step(x[:, :, t].contiguous()), seq[t]) for t in range(T + 3, T + 5))
+
+
+@pytest.mark.parametrize("update", [True, False], ids=["update", "peek"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_loop_in_a_graph(dt, update):
+    """A call that runs as single steps, recorded into a graph: one that would
+    allocate (the ring's backup, copies of frames at odd strides) takes a launch
+    that needs no memory instead.  Every replay, with eager work in between,
+    gives the outputs and the state of the eager call from the same state."""
+    B, C, T = 4, 192, 3
+    say("loop in a graph", dt, update)
+    g = torch.Generator(device=DEV).manual_seed(98800 + update)
+    tdt = synth.torch_dtype(dt)
+    x = torch.randn((B, C, T + 2, 7, 7), generator=g, device=DEV).to(tdt)
+    w = (torch.randn((C, C, 3, 3, 3), generator=g, device=DEV) * 0.05).to(tdt)
+    eager, co = (coinf.CoConv(w, None, batch=B, in_size=(7, 7), padding=(0, 1, 1))
+                 for _ in range(2))
+    assert co.steps_route(T, update_state=update) == "loop"
+    for t in range(2):
+        eager.forward_step(x[:, :, t].contiguous())
+        co.forward_step(x[:, :, t].contiguous())
+    buf, start = x[:, :, 2:].contiguous(), eager.state.clone()
+    want = eager.forward_steps(buf, update_state=update)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = co.forward_steps(buf, update_state=update)
+    for _ in range(3):
+        co.state.copy_(start)
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(co.state, eager.state)
+        assert torch.isfinite(buf.float().sum())
