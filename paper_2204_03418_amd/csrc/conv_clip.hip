@@ -28,17 +28,21 @@
 // waves that use them, one k-step ahead.  Units are swizzled by pixel so that
 // 8 lanes' operand reads fall into distinct banks.
 //
-// Three workgroups share a CU (two where their registers or the window below
-// need it): a workgroup's prologue, barriers and epilogue are long against its
-// K loop, and with one resident workgroup of eight waves the same tiles took
+// Up to three workgroups share a CU (two where their registers or the window
+// below need it): a workgroup's prologue, barriers and epilogue are long against
+// its K loop, and with one resident workgroup of eight waves the same tiles took
 // half as long again (192 -> 432 channels, 1x1x1, 7x7, 16 streams, 64 frames: 45
-// us against 31 us).  What bounds it then is the weights' way through L1:
-// a wave tile of 64 x 64 reads 4 KB of weights for 16 matrix instructions, at
-// the full 64 B a cycle of a CU's four waves as long as the instructions take.
+// us against 31 us).  That layer is then bound by the round trips of its
+// workgroups, 2000 of six k-steps each: the pixels' gather, a barrier a k-step
+// and the epilogue; the weights' way through L1 (4 KB for 16 matrix
+// instructions of a 64 x 64 wave tile) is about 4 us of it.  float32 is bound by
+// its matrix instructions while the CUs have a workgroup each, and after that by
+// the second pass of the workgroups that own ring slots (about 41 of 227 us in
+// the layer below, 32 workgroups of 480).
 //
-// Measured against single steps: that layer 455 -> 31 us; 128 -> 128, (9,1), 25
-// joints, 16 streams, 150 frames, float32 839 -> 227 us; 64 -> 64 bf16, 32
-// streams, 300 frames 2264 -> 44 us.
+// Measured against single steps: the pointwise layer 455 -> 31 us; 128 -> 128,
+// (9,1), 25 joints, 16 streams, 150 frames, float32 839 -> 227 us; 64 -> 64 bf16,
+// 32 streams, 300 frames 2264 -> 44 us.
 //
 // The ring.  Output tau's partial sum lives in slot tau mod R, and an output
 // that the call leaves unfinished may take the slot of one that it completes.

@@ -27,7 +27,8 @@
 // and L1 pipes: 112 wave loads for a k-step of 128 pixels x 96 channels, about
 // 1000 of its 1200 cycles at three workgroups a CU, where the matrix
 // instructions take 200.  192-channel tiles halve the pixels' share but leave
-// two workgroups a CU (321 us against 277 in the first measure below).
+// two workgroups a CU (321 us against 277 when both were built; the kernel took
+// 253 us after that, in the first measure below).
 //
 // Measured against a thread per output and a launch per frame: 96 -> 192,
 // 3x3x3, spatial stride 2, 28x28, 16 streams, bf16: 16 frames 12.2 ms -> 253

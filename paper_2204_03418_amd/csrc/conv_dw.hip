@@ -292,11 +292,11 @@ __global__ __launch_bounds__(kBlock) void conv_steps_dw_kernel(
 // the weights are scalar registers and leave the chip full of waves.
 //
 // What bounds it: 27 multiply-adds per output and frame (about 80 vector
-// instructions per pair, 22 us of the 37 in the first measure), then the
+// instructions per pair, 22 us of the 42 in the first measure), then the
 // frames' way from and to memory.  Four outputs a thread save loads but leave
 // rows ragged and half the waves (43 us against 42.5, 14x14 above 56 against
 // 47).  Measured, both ways with the call's own cost: 16 streams, 28x28, 108
-// channels, kT 3, 16 frames 61 -> 42.5 us; 4 streams, 14x14, 432 channels, 64
+// channels, kT 3, 16 frames 61 -> 42 to 47 us; 4 streams, 14x14, 432 channels, 64
 // frames 86 -> 47; 16 streams, 56x56, 54 channels, 16 frames 108 -> 76.
 template <int KT>
 __global__ __launch_bounds__(kBlock) void conv_steps_dw2_kernel(

@@ -551,8 +551,8 @@ def test_depthwise_forward_steps_persistent(case):
 
 
 def _check_fused_steps(make, x, ref, tdt, what):
-    """forward_steps as one persistent launch: against the oracle with end
-    padding; bitwise against per-frame forward_step (same per-tap arithmetic
+    """forward_steps in one launch (of whichever kernel the call is routed to):
+    against the oracle with end padding; bitwise against per-frame forward_step (same per-tap arithmetic
     order), also after clean_state (stale ring contents); a clip from the
     stream's start followed by single steps (the partial sums the clip
     leaves are those stepping leaves), a clip continuing a state left by
@@ -618,8 +618,9 @@ REG_STEPS_CASES = [
 @pytest.mark.parametrize("case", REG_STEPS_CASES, ids=lambda c: "regsteps_" + "_".join(
     map(str, c[:3])) + "_" + c[6])
 def test_reg_forward_steps_persistent(case):
-    """The register-GEMM forward_steps as one persistent launch (partial sums
-    in accumulator registers across frames)."""
+    """Register-GEMM layers' forward_steps in one launch: the persistent
+    kernel (partial sums in accumulator registers across frames) or the GEMM
+    over the frames, as the call is routed."""
     B, cin, cout, k, size, p, dt, T = case
     say("reg steps", case)
     spec = synth.ConvSpec(batch=B, in_channels=cin, out_channels=cout, kernel=k, in_size=size,
@@ -652,10 +653,10 @@ REG_STRIDED_CASES = [
     map(str, c[:3])) + f"_{c[6]}_T{c[7]}_s{c[8]}d{c[9]}")
 def test_reg_forward_steps_strided(case):
     """Temporal stride or dilation above 1 on the register GEMM's 1x1
-    spatial shapes: forward_steps as one plan-driven persistent launch
-    (partial sums in LDS slots, the host's step plans); the long clip is
-    split into time segments, so the clip-then-steps check covers the last
-    segment's write-back of the ring."""
+    spatial shapes: forward_steps in one launch: the plan-driven persistent
+    kernel (partial sums in LDS slots, the host's step plans) or the GEMM over
+    the frames, as the call is routed; the clip-then-steps check covers the
+    write-back of the ring."""
     B, cin, cout, k, size, p, dt, T, sT, dT = case
     st = (sT,) + (1,) * (len(k) - 1)
     dil = (dT,) + (1,) * (len(k) - 1)
@@ -721,9 +722,8 @@ GEMM_STEPS_CASES = [
 @pytest.mark.parametrize("case", GEMM_STEPS_CASES, ids=lambda c: "gemmsteps_" + "_".join(
     map(str, c[:3])) + f"_k{c[3][0]}")
 def test_gemm_forward_steps_persistent(case):
-    """The LDS-tiled GEMM's forward_steps as one persistent launch (bf16):
-    a workgroup owns pixels x output channels x every temporal tap, the
-    partial sums stay in its registers across frames."""
+    """The LDS-tiled GEMM's forward_steps in one launch (bf16), persistent or
+    over the frames, as the call is routed."""
     B, cin, cout, k, size, p = case
     say("gemm steps", case)
     spec = synth.ConvSpec(batch=B, in_channels=cin, out_channels=cout, kernel=k, in_size=size,
@@ -748,9 +748,10 @@ REG_SEG_CASES = [
 
 @pytest.mark.parametrize("case", REG_SEG_CASES, ids=lambda c: f"regseg_{c[0]}_{c[1]}_{c[2]}_T{c[6]}")
 def test_reg_forward_steps_time_segments(case):
-    """The persistent register GEMM over a clip long enough to be split into
-    time segments (each after the first replays kT - 1 frames and stores
-    from its own first frame): against the oracle with end padding on
+    """Register-GEMM layers over a clip long enough to be split into time
+    segments by the persistent kernel (each after the first replays kT - 1
+    frames and stores from its own first frame); the GEMM over the frames
+    where the call is routed to it: against the oracle with end padding on
     sampled streams, bitwise against stepping on all, as a clip that
     continues single steps, and with update_state=False."""
     B, cin, cout, k, size, p, T, dt, sel = case
@@ -832,7 +833,7 @@ POOL_STEPS_CASES = [
     ("avg", (3, 3, 2), (7, 6), (1, 2, 1), (1, 1, 0), False, "f32"),
     ("max", (5, 3, 3), (6, 5), (1, 1, 1), (2, 1, 1), True, "f32"),
     ("max", (1, 2, 2), (4, 4), (1, 2, 2), (0, 0, 0), True, "bf16"),
-    # global spatial pools (frames in lanes), clips over several 32-frame blocks
+    # global spatial pools (frames in lanes), clips over one and several 64-frame blocks
     ("avg", (4, 7, 7), (7, 7), (1, 7, 7), (0, 0, 0), False, "bf16", 75),
     ("max", (3, 6, 6), (6, 6), (1, 1, 1), (1, 0, 0), True, "f32", 40),
     ("avg", (2, 5, 5), (5, 5), (1, 5, 5), (0, 0, 0), True, "bf16", 33),
