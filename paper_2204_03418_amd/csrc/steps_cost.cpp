@@ -17,8 +17,8 @@
 // call to call.  A clip of 300 frames beyond about 100 MB counts with the mean
 // of changing and of repeated frames: the bf16 persistent kernels gain a third
 // from frames that the memory-side cache holds, the GEMM a tenth.  Taking the
-// cheapest by these estimates costs 0.6% over the best way on average, less than
-// 2% in 95 of 100 calls and 1.5x in the worst.
+// cheapest by these estimates costs 0.5% over the best way on average, less than
+// 1% in 95 of 100 calls and 1.3x in the worst.
 #include <algorithm>
 
 #include "launch.hpp"
@@ -74,15 +74,16 @@ int clip_tile(const ConvGeom& g, int64_t outputs) {
 // a workgroup each, and beyond that `rate` for every workgroup on the fullest
 // CU, in proportion to its channels (bf16 tiles narrower than 96 channels cost
 // as much).  The second pass (tail: the state is updated) walks the taps of the
-// unfinished outputs.
+// unfinished outputs and writes the ring, which calls shorter than kT, all of
+// whose outputs began before them, read first.
 double clip_us(const ConvGeom& g, int64_t frames, bool tail) {
   struct Fit {
-    double start, second, latency, per_tile, rate;
+    double start, second, latency, per_tile, rate, open, ring_mb;
   };
   const bool bf = g.dtype == CO_BF16;
-  const Fit f = !bf             ? Fit{6.64, 1.99, 0.312, 0.906, 1.015}
-                : clip_pairs(g) ? Fit{7.66, 4.37, 0.158, 0.429, 0.368}
-                                : Fit{6.22, 3.33, 0.439, 0.282, 0.461};
+  const Fit f = !bf             ? Fit{6.67, 1.66, 0.312, 0.906, 1.015, 0.68, 0.60}
+                : clip_pairs(g) ? Fit{7.86, 3.75, 0.131, 0.406, 0.355, 2.68, 0.67}
+                                : Fit{6.58, 2.81, 0.439, 0.267, 0.447, 0.14, 0.61};
   const int64_t outputs = ceil_div(frames, g.sT);
   const int tile = clip_tile(g, outputs);
   const double q = double(g.kH) * g.kW * ceil_div(g.Cin, bf ? 32 : 16);
@@ -96,22 +97,39 @@ double clip_us(const ConvGeom& g, int64_t frames, bool tail) {
   if (tail && g.kT > 1) {
     const int64_t open = ceil_div(g.kT - 1, g.sT);  // unfinished outputs
     const int64_t taps = std::min<int64_t>(g.kT - 1, frames + (open - 1) * g.sT);
-    us += f.second + ksteps(double(taps), g.R);
+    const double ring = f.ring_mb * 4e-6 * double(g.R) * g.B * g.So() * g.Cout;
+    us += f.second + ksteps(double(taps), g.R) + ring;
+    if (frames < g.kT) us += f.open + ring;
   }
   return std::max(us, kCallUs);
 }
 
-// Single steps: a launch, or what its kernel takes.
+// Single steps: a launch, or what its kernel takes.  The register GEMM's time
+// goes with the waves that a SIMD gets and the k-steps of a wave.
 double loop_us(const ConvGeom& g, int64_t frames) {
-  const double mflops = 2e-6 * g.B * g.So() * g.Cout * g.kT * g.Cin * g.kH * g.kW / g.sT;
   double us;
+  RegConfig r;
   if (g.algo == CO_ALGO_GEMM_REG) {
-    us = 4.6 + mflops / (g.dtype == CO_BF16 ? 100 : 75);
+    if (!reg_config(g, g.cfg, &r)) return 0;
+    struct Fit {
+      double start, wave, kstep;
+    };
+    const Fit f = r.id == 0   ? Fit{5.38, 0.415, 0.108}
+                  : r.id == 1 ? Fit{4.47, 1.245, 0.023}
+                  : r.id == 5 ? Fit{4.47, 0.733, 0.497}
+                  : r.id == 6 ? Fit{3.70, 1.025, 0.107}
+                  : r.id == 7 ? Fit{4.39, 1.350, 0.172}
+                  : r.id == 8 ? Fit{4.78, 2.292, 0.034}
+                  : r.id == 9 ? Fit{3.71, 0.533, 0.159}
+                              : Fit{4.60, 1.200, 0};
+    const double waves = double(r.m_frags) * ceil_div(r.n_frags, r.WN) * r.KSPLIT / g.sT;
+    us = f.start + waves / 1024 * (f.wave + f.kstep * r.KS);
   } else {
     GemmConfig c;
     if (!gemm_config(g, g.cfg, &c)) return 0;
     const double taps = double(g.kH) * g.kW, chunks = c.n_chunks;
     if (c.M_WG == 448) {
+      const double mflops = 2e-6 * g.B * g.So() * g.Cout * g.kT * g.Cin * taps / g.sT;
       us = 9 + 0.21 * taps * chunks + mflops / 1450;
     } else {
       // tiles of 32 x 128 (bf16, float32) and 64 x 16 (float32): a chunk of
@@ -127,7 +145,7 @@ double loop_us(const ConvGeom& g, int64_t frames) {
                         tiles * (f.tile + chunks * (f.r0 + f.r1 * taps)));
     }
   }
-  return 3 + double(frames) * std::max(us, 5.0);
+  return std::max(6 + 3.6 * frames, 1 + double(frames) * std::max(us, 5.1));
 }
 
 // The register GEMM's persistent kernels of one spatial tap (conv_reg.hip):
@@ -158,7 +176,7 @@ double reg_steps_us(const ConvGeom& g, const RegConfig& c, int64_t frames) {
     double start, once, load, frame, per, mb;
   };
   const Fit f = c.id == 0   ? Fit{8.00, 0, 0.131, 0.300, 0.011, 0.300}
-                : c.id == 1 ? Fit{8.30, 0.039, 0.039, 1.451, 0, 0.196}
+                : c.id == 1 ? Fit{7.60, 0.039, 0.039, 1.451, 0, 0.196}
                 : c.id == 5 ? Fit{8.00, 0.168, 0.168, 0.300, 0, 0.347}
                             : Fit{8.05, 0.131, 0.131, 0.651, 0, 0};
   const double rounds = double(ceil_div(wgs * sw * segs, 1024 * wpe));
@@ -167,11 +185,11 @@ double reg_steps_us(const ConvGeom& g, const RegConfig& c, int64_t frames) {
                                f.mb * mb);
 }
 
-// The persistent 3x3 GEMM: about 3.3 us a frame and 32 channels for every 256
+// The persistent 3x3 GEMM: about 3.2 us a frame and 32 channels for every 256
 // workgroups (160 pixels x 64 channels).
 double gemm_steps_us(const GemmStepsConfig& c, int64_t frames) {
   const double rounds = double(ceil_div(int64_t(c.m_tiles) * c.o_tiles, 256));
-  return 8 + double(frames) * rounds * c.n_chunks * 3.3;
+  return 8 + double(frames) * rounds * c.n_chunks * 3.2;
 }
 
 StepsRoute cheapest_steps(const ConvGeom& g, int64_t frames, StepsMode mode, bool clip, bool gemm,
